@@ -360,8 +360,12 @@ int hydro_autotune(const struct hydro_spec* spec, int n_groups_hint, void* strea
  * Depths 2 and 4 are built for the FP32 van Leer / characteristic
  * specialization with variant 4 only (CTU with PLM or PPM, MHM and VL with
  * PPM); the depth used is the largest built one, not above the request, that
- * divides the box's group count in z.  At one tile depth, results do not
- * depend on the grid or variant (bit for bit).  Tile depths differ in the
+ * divides the box's group count in z.  A launch of one group per workgroup
+ * with too few groups to fill the device splits each group's planes over
+ * several workgroups (variant 4 in FP32, 2 in FP64, no smaller grid pinned);
+ * hydro_get_launch_shape reports the workgroups it uses.  At one tile depth,
+ * results and diagnostic counts do not depend on the grid, the variant or a
+ * split (bit for bit).  Tile depths differ in the
  * last bits on the first planes of a group that continues a run, whose z
  * slopes and edges come from the kernel's loop body rather than its z
  * prologue (two copies of the same arithmetic the compiler may contract

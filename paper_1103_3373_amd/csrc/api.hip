@@ -169,6 +169,8 @@ struct Tune {
   int waves;     // 2 or 4
   int zrun;      // CTU box steps: groups per z-run (0 = default)
   int grid_box;  // CTU box steps: workgroups (0 = as grid)
+  int zsplit = 1;       // workgroups per group along z (chosen per launch, never stored)
+  int zsplit_pred = 1;  // the same of the VL predictor
 };
 std::map<std::string, Tune> g_tune;
 bool g_tune_loaded = false;
@@ -204,6 +206,34 @@ int cu_count() {
   cache[dev] = cus;
   return cus;
 }
+// Workgroups per group along z for a launch of n groups, `slots` (1 or 2)
+// resident per compute unit.  A workgroup that marches nz planes takes about
+// nz + extra plane times (the planes beside its own and the start of its z
+// window), so a split pays only while it fills units that would stand idle.
+// The model is the time of the fullest unit, with m = ceil(items / units)
+// workgroups: a pair that shares a unit takes 1.42 times as long as one alone
+// (measured at 256^3 cells per second: CTU 171 against 120 us for 512 and 256
+// groups, MHM 122 against 85).  Its choice is within 6% of the best s of a
+// sweep over 8 to 1000 groups: 120 us become 28 at 8 groups, 49 at 64 and 108
+// at 216 (CTU, FP32).  A larger s has to be 3% better.  A batched launch
+// (shared) may run beside others on other streams, to which the planes a split
+// repeats are lost: it stops at one workgroup per unit (a server tick over 6
+// classes of 64 to 520 groups: 500 us, 549 us with the full rule).
+int split_for(long long n, int slots, double extra, bool shared) {
+  const int cus = cu_count();
+  int best = 1;
+  double best_cost = 1e300;
+  for (int s = 1; s <= 16; ++s) {
+    const long long m = (n * s + cus - 1) / cus;
+    if (shared && s > 1 && m > 1) break;
+    const int longest = (16 + s - 1) / s;
+    const double planes = (m == 1 ? longest : 0.5 * (longest + 16.0 / s)) + extra;
+    const double cost = planes * (slots == 1 ? (double)m : 1.42 * (double)(m / 2) + (double)(m % 2));
+    if (cost < 0.97 * best_cost) { best_cost = cost; best = s; }
+  }
+  return best;
+}
+
 Tune tuned(int f64, int scheme, int recon, int riemann, int charlim, long long n_groups) {
   tune_load();
   auto it = g_tune.find(tune_key(f64, scheme, recon, riemann, charlim));
@@ -216,6 +246,16 @@ Tune tuned(int f64, int scheme, int recon, int riemann, int charlim, long long n
   if (t.grid <= 0) t.grid = cu_count() * (t.waves == 4 ? 12 : 1);
   if (t.grid > n_groups) t.grid = (int)n_groups;
   if (t.grid < 1) t.grid = 1;
+  return t;
+}
+
+// Splits the groups of a one-group-per-item launch along z where it has too
+// few of them (and no smaller grid is pinned).
+Tune split_small(Tune t, int f64, int scheme, long long n_groups, bool shared = false) {
+  if (t.grid < n_groups || t.waves != hy::split_waves(f64)) return t;
+  t.zsplit = split_for(n_groups, f64 ? 1 : 2, 3.4, shared);
+  t.grid = (int)(n_groups * t.zsplit);
+  if (scheme == HYDRO_VL) t.zsplit_pred = split_for(n_groups, 2, 1.5, shared);
   return t;
 }
 
@@ -239,13 +279,14 @@ Tune tuned_box(int f64, int scheme, int recon, int riemann, int limiter, int cha
   const long long items = n_groups / K;
   if (t.grid > items) t.grid = (int)items;
   if (t.grid < 1) t.grid = 1;
-  return t;
+  return K == 1 ? split_small(t, f64, scheme, n_groups) : t;
 }
 
 template <typename T>
 int run_fused(const hy::Seg* segs_dev, int n_segs, long long n_groups, int g, int scheme, int recon, int riemann,
-              int limiter, int flags, double gamma, unsigned long long* diag, int grid, int waves, hipStream_t st,
-              void* wstar, const hy::Seg* seg0 = nullptr, double dt0 = 0.0, int wstar_box = 0, int zrun = 1) {
+              int limiter, int flags, double gamma, unsigned long long* diag, const Tune& tu, hipStream_t st, void* wstar,
+              const hy::Seg* seg0 = nullptr, double dt0 = 0.0, int wstar_box = 0, int zrun = 1) {
+  const int grid = tu.grid;
   hy::FusedArgs<T> a;
   a.segs = segs_dev;
   a.n_segs = n_segs;
@@ -265,12 +306,15 @@ int run_fused(const hy::Seg* segs_dev, int n_segs, long long n_groups, int g, in
   a.wstar = reinterpret_cast<T*>(wstar);
   a.wstar_box = wstar_box;
   a.zrun = zrun;
+  a.zsplit = tu.zsplit;
   hy::FusedCfg cfg;
   cfg.grid = grid;
-  cfg.waves = waves;
-  // The VL predictor takes one group per work item: as many workgroups as
-  // the second stage has groups in flight.
-  cfg.grid_pred = (int)std::min<long long>(n_groups, (long long)grid * zrun);
+  cfg.waves = tu.waves;
+  // The VL predictor takes one group (or chunk of one) per work item: as many
+  // workgroups as the second stage has groups in flight.
+  cfg.zsplit_pred = tu.zsplit_pred;
+  cfg.grid_pred = tu.zsplit_pred > 1 ? (int)(n_groups * tu.zsplit_pred)
+                                     : (int)std::min<long long>(n_groups, (long long)grid * zrun);
   hipError_t e = hy::launch_fused(a, scheme, recon, riemann, cfg, st);
   if (e != hipSuccess) return hip_fail(e, "fused solver launch");
   return 0;
@@ -366,13 +410,14 @@ int hydro_solve_groups(const void* in, void* out, void* flux_out, int n_groups, 
   }
   // Fused path: a single segment passed by value, host dt included.
   hy::Seg seg{in, out, flux_out, nullptr, 1.0, dh, 0, n_groups, 0, 0, 0, 0};
-  const Tune tu = tuned(f64, scheme, reconstruction, riemann, (flags & HYDRO_CHAR) ? 1 : 0, n_groups);
+  const Tune tu = split_small(tuned(f64, scheme, reconstruction, riemann, (flags & HYDRO_CHAR) ? 1 : 0, n_groups), f64,
+                              scheme, n_groups);
   if (int rc = ensure_vl(w, (size_t)n_groups * hy::fused_scratch_per_group(scheme, reconstruction, 0) * esz)) return rc;
   if (f64)
     return run_fused<double>(nullptr, 1, n_groups, g, scheme, reconstruction, riemann, limiter, flags, gamma,
-                             ds->diag, tu.grid, tu.waves, st, w.vl, &seg, dt);
-  return run_fused<float>(nullptr, 1, n_groups, g, scheme, reconstruction, riemann, limiter, flags, gamma, ds->diag,
-                          tu.grid, tu.waves, st, w.vl, &seg, dt);
+                             ds->diag, tu, st, w.vl, &seg, dt);
+  return run_fused<float>(nullptr, 1, n_groups, g, scheme, reconstruction, riemann, limiter, flags, gamma, ds->diag, tu,
+                          st, w.vl, &seg, dt);
 }
 
 int hydro_solve_batch(const struct hydro_seg* segs, int n_segs, long long n_groups_total,
@@ -396,7 +441,8 @@ int hydro_solve_batch(const struct hydro_seg* segs, int n_segs, long long n_grou
   if (int rc = device_state(&ds)) return rc;
   const bool f64 = (spec->flags & HYDRO_F64) != 0;
   const int g = ghost_width(spec->scheme, spec->reconstruction);
-  const Tune tu = tuned(f64, spec->scheme, spec->reconstruction, spec->riemann, charlim, n_groups_total);
+  const Tune tu = split_small(tuned(f64, spec->scheme, spec->reconstruction, spec->riemann, charlim, n_groups_total),
+                              f64, spec->scheme, n_groups_total, true);
   Workspace& w = ds->ws[st];
   const int box_segs = (spec->flags & HYDRO_BOX_SEGS) ? 1 : 0;
   if (int rc = ensure_vl(w, (size_t)n_groups_total *
@@ -406,11 +452,9 @@ int hydro_solve_batch(const struct hydro_seg* segs, int n_segs, long long n_grou
   const hy::Seg* sd = (const hy::Seg*)segs;
   if (f64)
     return run_fused<double>(sd, n_segs, n_groups_total, g, spec->scheme, spec->reconstruction, spec->riemann,
-                             spec->limiter, spec->flags, spec->gamma, ds->diag, tu.grid, tu.waves, st, w.vl, nullptr,
-                             0.0, box_segs);
+                             spec->limiter, spec->flags, spec->gamma, ds->diag, tu, st, w.vl, nullptr, 0.0, box_segs);
   return run_fused<float>(sd, n_segs, n_groups_total, g, spec->scheme, spec->reconstruction, spec->riemann,
-                          spec->limiter, spec->flags, spec->gamma, ds->diag, tu.grid, tu.waves, st, w.vl, nullptr, 0.0,
-                          box_segs);
+                          spec->limiter, spec->flags, spec->gamma, ds->diag, tu, st, w.vl, nullptr, 0.0, box_segs);
 }
 
 int hydro_step_box(const void* box_in, void* box_out, void* flux_out, int nx, int ny, int nz, const double* dt_dev,
@@ -445,11 +489,10 @@ int hydro_step_box(const void* box_in, void* box_out, void* flux_out, int nx, in
   if (int rc = device_state(&ds)) return rc;
   hy::Seg seg{box_in, box_out, flux_out, dt_dev, dt_scale, dh, 0, G, nx / 16, ny / 16, nz / 16, 1};
   const int g = ghost_width(scheme, reconstruction);
-  // CTU without flux output marches through runs of z-consecutive groups.
   // Without flux output the workgroups march through runs of z-consecutive
   // groups.
   const Tune tu = !flux_out ? tuned_box(f64, scheme, reconstruction, riemann, limiter, charlim, G, nz / 16)
-                            : tuned(f64, scheme, reconstruction, riemann, charlim, G);
+                            : split_small(tuned(f64, scheme, reconstruction, riemann, charlim, G), f64, scheme, G);
   const int zrun = !flux_out ? tu.zrun : 1;
   Workspace& w = ds->ws[st];
   if (int rc = ensure_vl(w, (size_t)G * hy::fused_scratch_per_group(scheme, reconstruction, 1) * esz)) return rc;
@@ -457,10 +500,10 @@ int hydro_step_box(const void* box_in, void* box_out, void* flux_out, int nx, in
   // a device dt pointer in seg0).
   // VL: the half step is computed once per cell of the box (wstar_box).
   if (f64)
-    return run_fused<double>(nullptr, 1, G, g, scheme, reconstruction, riemann, limiter, flags, gamma, ds->diag,
-                             tu.grid, tu.waves, st, w.vl, &seg, -1.0, 1, zrun);
-  return run_fused<float>(nullptr, 1, G, g, scheme, reconstruction, riemann, limiter, flags, gamma, ds->diag, tu.grid,
-                          tu.waves, st, w.vl, &seg, -1.0, 1, zrun);
+    return run_fused<double>(nullptr, 1, G, g, scheme, reconstruction, riemann, limiter, flags, gamma, ds->diag, tu,
+                             st, w.vl, &seg, -1.0, 1, zrun);
+  return run_fused<float>(nullptr, 1, G, g, scheme, reconstruction, riemann, limiter, flags, gamma, ds->diag, tu, st,
+                          w.vl, &seg, -1.0, 1, zrun);
 }
 
 int hydro_cfl_dt(const void* U, int n_groups, double dh, double gamma, double cfl, int flags, double* dt_out,
@@ -850,10 +893,11 @@ int hydro_autotune(const struct hydro_spec* spec, int n_groups_hint, void* strea
       float ms_min = 1e30f;
       for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
         e = hipEventRecord(e0, st);
+        const Tune tu{(int)grid, wv, 0, 0};
         int rc = f64 ? run_fused<double>(sd, 1, n, g, spec->scheme, spec->reconstruction, spec->riemann,
-                                         spec->limiter, spec->flags, spec->gamma, ds->diag, (int)grid, wv, st, vl)
+                                         spec->limiter, spec->flags, spec->gamma, ds->diag, tu, st, vl)
                      : run_fused<float>(sd, 1, n, g, spec->scheme, spec->reconstruction, spec->riemann,
-                                        spec->limiter, spec->flags, spec->gamma, ds->diag, (int)grid, wv, st, vl);
+                                        spec->limiter, spec->flags, spec->gamma, ds->diag, tu, st, vl);
         if (rc) { e = hipErrorLaunchFailure; break; }
         if (e == hipSuccess) e = hipEventRecord(e1, st);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -898,12 +942,13 @@ int hydro_autotune(const struct hydro_spec* spec, int n_groups_hint, void* strea
         float ms_min = 1e30f;
         for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
           e = hipEventRecord(e0, st);
+          const Tune tu{(int)grid, best.waves, 0, 0};
           int rc = f64 ? run_fused<double>(nullptr, 1, n, g, spec->scheme, spec->reconstruction, spec->riemann,
-                                           spec->limiter, spec->flags, spec->gamma, ds->diag, (int)grid, best.waves,
-                                           st, vl, &bs, -1.0, 1, zr)
+                                           spec->limiter, spec->flags, spec->gamma, ds->diag, tu, st, vl, &bs, -1.0, 1,
+                                           zr)
                        : run_fused<float>(nullptr, 1, n, g, spec->scheme, spec->reconstruction, spec->riemann,
-                                          spec->limiter, spec->flags, spec->gamma, ds->diag, (int)grid, best.waves,
-                                          st, vl, &bs, -1.0, 1, zr);
+                                          spec->limiter, spec->flags, spec->gamma, ds->diag, tu, st, vl, &bs, -1.0, 1,
+                                          zr);
           if (rc) { e = hipErrorLaunchFailure; break; }
           if (e == hipSuccess) e = hipEventRecord(e1, st);
           if (e == hipSuccess) e = hipEventSynchronize(e1);

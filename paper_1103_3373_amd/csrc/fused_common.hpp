@@ -199,6 +199,30 @@ HY_DEV USeg find_seg(const FusedArgs<T>& a, long long grp, int& seg, double& dt)
   return u;
 }
 
+// Work items of a launch that splits its groups along z (FusedArgs::zsplit =
+// n > 1): chunk j of n covers the group's planes z0 .. z0 + nz - 1.  Results
+// keep the bits of an unsplit group: a chunk that starts inside the group
+// fills its z window by running the plane loop's own column work a few planes
+// early, not the z prologue (inlined copies of the same arithmetic may be
+// contracted differently).  A chunk repeats the z work of the planes beside it
+// that its neighbours own; only one of them counts its diagnostics: chunk
+// iteration t (plane z0 + t) counts if the plane is the chunk's own, or the
+// group's plane -1 or 16 at its ends, so the totals are those of an unsplit
+// group.
+struct Chunk {
+  int z0, nz;
+  bool first, last;
+  HY_DEV bool counts(int t) const { return (t >= 0 || first) && (t < nz || last); }
+};
+HY_DEV Chunk chunk_of(int j, int n) {
+  Chunk c;
+  c.z0 = uni(j * 16 / n);
+  c.nz = uni((j + 1) * 16 / n) - c.z0;
+  c.first = j == 0;
+  c.last = j == n - 1;
+  return c;
+}
+
 // Box segments address a cell by a 32-bit byte offset within a z-slab of
 // groups (ngx * ngy groups), so a slab must hold less than 4 GiB; a segment
 // beyond that gets NaN outputs.
@@ -240,6 +264,11 @@ template <typename T, int G> struct ColumnReader {
       bz0 = bnz = 0;
       zgs = 0;
     }
+  }
+  // Planes are counted from plane z0 of the group from here on.
+  HY_DEV void start_at(int z0) {
+    bz0 += z0;
+    if (!box) base += (long)z0 * N * N * (long)sizeof(T);
   }
   HY_DEV V5<T> load(int z) const {
     V5<T> u;

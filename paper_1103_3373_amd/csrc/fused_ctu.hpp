@@ -111,7 +111,9 @@ template <typename T> HY_DEV V5<T> other_frame_d(const V5<T>& v, bool d) {
 // every other combination runs the same code with run-time choices.
 //
 // ZR: groups per work item (tile depth 16 * ZR): ZR > 1 only for a single
-// periodic box without flux output (a.zrun == ZR).
+// periodic box without flux output (a.zrun == ZR).  ZR = 0: a work item is a
+// chunk of a group, 1/a.zsplit of its planes, for launches with too few
+// groups to fill the chip.
 template <typename T, bool PPM, int RS, int WAVES, bool FAST, int ZR>
 __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T> a) {
   constexpr int NT = kThreads;
@@ -158,14 +160,22 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
   // Work items: single groups, or runs of ZR z-consecutive groups of one
   // periodic box (flux output off), marched through in one pass: the z
   // prologue and the two planes beyond each end are paid once per run.
-  constexpr int nzt = 16 * ZR;  // interior planes of an item
+  constexpr bool SPLIT = ZR == 0;
+  constexpr int KR = SPLIT ? 1 : ZR;
   int seg = 0;
-  const GroupOrder order = group_order(a.n_groups / ZR);
+  const GroupOrder order = group_order(SPLIT ? a.n_groups * a.zsplit : a.n_groups / KR);
   for (long long item = order.first; item < order.end; item += order.stride) {
     double dt;
-    const USeg S = find_seg(a, item * ZR, seg, dt);
-    long long lg = item * ZR - S.first;  // the item's first group (local)
-    int gzs = 0;                           // groups between z neighbours
+    long long grp = item * KR;  // the item's first group
+    Chunk ck{0, 16 * KR, true, true};
+    if constexpr (SPLIT) {
+      grp = uni((int)((unsigned)item / (unsigned)a.zsplit));
+      ck = chunk_of((int)(item - grp * a.zsplit), a.zsplit);
+    }
+    const int z0 = SPLIT ? ck.z0 : 0, nzt = SPLIT ? ck.nz : 16 * KR;  // the item's interior planes
+    const USeg S = find_seg(a, grp, seg, dt);
+    long long lg = grp - S.first;  // (local)
+    int gzs = 0;                   // groups between z neighbours
     if constexpr (ZR > 1) {
       // item -> (column c, run r) of the box; group (r ZR + j) nxy + c
       const int nxy = S.ngx * S.ngy, li = (int)(item - S.first / ZR);
@@ -173,7 +183,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
       gzs = nxy;
     }
     T* __restrict__ O = reinterpret_cast<T*>(S.out) + lg * 5 * 4096;
-    T* __restrict__ FO = (ZR == 1 && S.flux) ? reinterpret_cast<T*>(S.flux) + lg * 3 * a.nf * 5 * 256 : nullptr;
+    T* __restrict__ FO = (ZR <= 1 && S.flux) ? reinterpret_cast<T*>(S.flux) + lg * 3 * a.nf * 5 * 256 : nullptr;
     // A box segment beyond the addressing limit gets NaN outputs: a NaN dt/dh
     // makes every updated cell NaN, and the face fluxes get NaN added.
     const T poison = slab_fits<T>(S) ? T(0) : T(__builtin_nan(""));
@@ -183,6 +193,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
     // box mode, straight from the periodic grouped box.
     ColumnReader<T, G> rd;
     rd.init(S, lg, col.x, col.y);
+    if constexpr (SPLIT) rd.start_at(z0);
     if (!cross) {
       // Each thread reads back only the slots it writes: no barrier needed.
       for (int c = tid; c < nCols; c += NT - 320) {
@@ -210,13 +221,34 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
     const int zlast = nzt + ahead - 1;
 
     // ---- prologue: window and traced states of plane -1 -------------------
-    if (cross) {
+    // A chunk inside the group starts warm planes early: its first iterations
+    // do the column work alone, until the traced states of plane -1 are there.
+    // Near the group's bottom it takes the group's own prologue (PPM: its
+    // slopes of planes -2 .. 0 are still needed).
+    constexpr int warm = PPM ? 3 : 1;
+    const bool head = !SPLIT || z0 <= (PPM ? 2 : 0);
+    const int zb = SPLIT ? -z0 : 0;  // the group's plane 0 in a head chunk
+    const int tfirst = head ? zb - 1 : -1 - warm;
+    if (!head) {
+      if (cross) {
+        if (PPM) {
+          w1 = zprim(-3);
+          w2 = zprim(-2);
+        } else {
+          w0 = zprim(-2);
+          w1 = zprim(-1);
+        }
+        unext = load_cons(-1 - warm + ahead);
+        s1 = e0 = ztm = ztp = h1m = V5<T>{};
+        if (PPM) w0 = w1;
+      }
+    } else if (cross) {
       if (PPM) {
-        V5<T> wa = zprim(-3), wb = zprim(-2);
-        w0 = zprim(-1);
-        w1 = zprim(0);
-        w2 = zprim(1);
-        unext = load_cons(-1 + ahead);
+        V5<T> wa = zprim(zb - 3), wb = zprim(zb - 2);
+        w0 = zprim(zb - 1);
+        w1 = zprim(zb);
+        w2 = zprim(zb + 1);
+        unext = load_cons(zb - 1 + ahead);
         V5<T> sa = slope<PPM>(wa, wb, w0, ph), sb = slope<PPM>(wb, w0, w1, ph);
         s1 = slope<PPM>(w0, w1, w2, ph);
         ztm = ppm_edge(wb, w0, sa, sb);
@@ -225,20 +257,23 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
         ppm_mono(w0, ztm, ztp);
         ctu_trace<true>(w0, ztm, ztp, ph);
       } else {
-        V5<T> wb = zprim(-2);
-        w0 = zprim(-1);
-        w1 = zprim(0);
-        unext = load_cons(-1 + ahead);
+        V5<T> wb = zprim(zb - 2);
+        w0 = zprim(zb - 1);
+        w1 = zprim(zb);
+        unext = load_cons(zb - 1 + ahead);
         V5<T> sb = slope<PPM>(wb, w0, w1, ph);
         plm_faces(wb, w0, w1, sb, ph, ztm, ztp);
         ctu_trace<false>(w0, ztm, ztp, ph);
       }
-      tally.floors_wave(floor_wave(ztm, ph) + floor_wave(ztp, ph));
+      const unsigned fl = floor_wave(ztm, ph) + floor_wave(ztp, ph);
+      if (ck.first) tally.floors_wave(fl);
     }
 
-    for (int t = -1; t <= nzt; ++t) {
+    for (int t = tfirst; t <= nzt; ++t) {
+      const bool counted = !SPLIT || ck.counts(t);
       // ---- A: columns: primitive plane t; trace plane t+1; H1(t+1/2) -------
       V5<T> nzm, nzp;  // traced states of plane t+1
+      const bool warming = SPLIT && t < -1;  // uniform
       if (cross) {
         const V5<T> wl = from_frame<2>(w0);
         sts5(sP, kP, pcol, wl);
@@ -247,7 +282,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
         // anyway, on a clamped plane index, so that the column's register
         // window advances the same way on every iteration (no copies at a
         // join); its diagnostics are not counted and its results are unused.
-        const bool live = t < nzt;
+        const bool live = t < nzt && counted;
         const V5<T> w3 = to_frame<2>(prim_of(unext, ph));  // plane min(t + ahead, zlast)
         unext = load_cons(t + 1 + ahead < zlast ? t + 1 + ahead : zlast);
         if (PPM) {
@@ -273,7 +308,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
         }
         if (t >= 0) sts5(sDH, kSQ, sqc, from_frame<2>(sub5(h1p, h1m)));
         h1m = h1p;
-      } else {
+      } else if (!warming) {
         // Ring corners and outer columns (column ids 320 .. nCols-1), strided
         // over the threads that own no cross column.
         for (int c = tid; c < nCols; c += NT - 320) {
@@ -284,6 +319,11 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
           sts5(sP, kP, (oc.y + G) * N + (oc.x + G), wl);
           sts5(sQ, kP, (oc.x + G) * N + (oc.y + G), to_frame<1>(wl));
         }
+      }
+      if (warming) {
+        ztm = nzm;
+        ztp = nzp;
+        continue;
       }
       __syncthreads();
 
@@ -326,7 +366,8 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
                     fr);
         }
         ctu_trace<PPM>(wc, fl, fr, ph);
-        tally.floors_wave(floor_wave(fl, ph) + floor_wave(fr, ph));
+        const unsigned hits = floor_wave(fl, ph) + floor_wave(fr, ph);
+        if (counted) tally.floors_wave(hits);
         sts5(w, kSQ, r, fl);
         sts5(w + 5 * kSQ, kSQ, r, fr);
       }
@@ -342,7 +383,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
         const int l = (b + 1) * 18 + (i + 1);
         int nf = 0;
         V5<T> F = riemann<RS>(lds5(w + 5 * kSQ, kSQ, l), lds5(w, kSQ, l + 1), ph, &nf);
-        tally.fails(nf);
+        if (counted) tally.fails(nf);
         sts5(sF1 + (d ? 5 * kF1 : 0), kF1, r, other_frame_d(F, d));
       }
       __syncthreads();
@@ -364,8 +405,10 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
         int nf = 0;
         V5<T> cm = correct(ztm, d, ph, nfl), cp = correct(ztp, d, ph, nfl);
         if (t >= 0) hn = from_frame<2>(riemann<RS>(zcp, cm, ph, &nf));  // H(t-1/2)
-        tally.floors_wave(nfl);
-        tally.fails(nf);
+        if (counted) {
+          tally.floors_wave(nfl);
+          tally.fails(nf);
+        }
         zcp = cp;
       }
       if (t >= 0 && t < nzt) {
@@ -407,7 +450,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
           // plane t-1 lies in the item's group (t-1)/16, at its z = (t-1)%16
           T* Og = O;
           if constexpr (ZR > 1) Og += (long)((t - 1) >> 4) * gzs * (5 * 4096);
-          const int o = (((t - 1) & 15) * 16 + y) * 16 + x;
+          const int o = (((z0 + t - 1) & 15) * 16 + y) * 16 + x;
 #pragma unroll
           for (int n = 0; n < 5; ++n) gstore(Og + n * 4096, (unsigned)o * (unsigned)sizeof(T), u[n] - ph.dtdh * (acc[n] + hn[n]));
         }
@@ -418,8 +461,10 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
           for (int n = 0; n < 5; ++n) acc[n] = (fx[n] + gy[n]) - hn[n];  // hn is the lower z face of plane t
         }
         if (FO) {
-          const int f = (t == 0) ? 0 : (t == 16 ? 1 : (t == 8 && a.nf == 3 ? 2 : -1));
-          if (f >= 0) {
+          // z face z0 + t of the group (a chunk's last face is the next one's first)
+          const int p = z0 + t;
+          const int f = (p == 0) ? 0 : (p == 16 ? 1 : (p == 8 && a.nf == 3 ? 2 : -1));
+          if (f >= 0 && (t >= 0 && (t < nzt || p == 16))) {
 #pragma unroll
             for (int n = 0; n < 5; ++n) gstore(FO + ((2 * a.nf + f) * 5 + n) * 256, (unsigned)(y * 16 + x) * (unsigned)sizeof(T), hn[n] + poison);
           }
@@ -432,7 +477,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
           const int fi = f == 0 ? -1 : (f == 1 ? 15 : 7);  // face index of offsets 0, 16, 8
           const V5<T> v = from_frame_d(lds5(sF2 + (d ? 5 * kF2 : 0), kF2, s * 17 + fi + 1), d);
 #pragma unroll
-          for (int n = 0; n < 5; ++n) gstore(FO + (((d ? 1 : 0) * a.nf + f) * 5 + n) * 256, (unsigned)(t * 16 + s) * (unsigned)sizeof(T), v[n] + poison);
+          for (int n = 0; n < 5; ++n) gstore(FO + (((d ? 1 : 0) * a.nf + f) * 5 + n) * 256, (unsigned)((z0 + t) * 16 + s) * (unsigned)sizeof(T), v[n] + poison);
         }
       }
       if (cross) {

@@ -20,6 +20,10 @@ static hipError_t launch_zr(const FusedArgs<float>& a, int grid, hipStream_t st)
 
 template <bool PPM, int RS, int WAVES, bool FAST>
 static hipError_t launch_one(const FusedArgs<float>& a, int grid, hipStream_t st) {
+  if (a.zsplit > 1) {
+    if constexpr (WAVES == 4) return launch_zr<PPM, RS, WAVES, FAST, 0>(a, grid, st);
+    return hipErrorInvalidValue;
+  }
   if constexpr (WAVES == 4 && FAST) {
     if (a.zrun == 2) return launch_zr<PPM, RS, WAVES, FAST, 2>(a, grid, st);
     if (a.zrun == 4) return launch_zr<PPM, RS, WAVES, FAST, 4>(a, grid, st);

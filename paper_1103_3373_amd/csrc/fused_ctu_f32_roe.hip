@@ -18,6 +18,10 @@ static hipError_t launch_roe_zr(const FusedArgs<float>& a, int grid, hipStream_t
 
 template <bool PPM, int WAVES, bool FAST>
 static hipError_t launch_roe(const FusedArgs<float>& a, int grid, hipStream_t st) {
+  if (a.zsplit > 1) {
+    if constexpr (WAVES == 4) return launch_roe_zr<PPM, WAVES, FAST, 0>(a, grid, st);
+    return hipErrorInvalidValue;
+  }
   if constexpr (WAVES == 4 && FAST) {
     if (a.zrun == 2) return launch_roe_zr<PPM, WAVES, FAST, 2>(a, grid, st);
     if (a.zrun == 4) return launch_roe_zr<PPM, WAVES, FAST, 4>(a, grid, st);

@@ -3,16 +3,22 @@
 
 namespace hy {
 
-template <bool PPM, int RS, int WAVES, bool FAST>
-static hipError_t launch_one(const FusedArgs<double>& a, int grid, hipStream_t st) {
-  if (a.zrun != 1) return hipErrorInvalidValue;  // one tile depth in FP64
-  auto k = ctu::ctu_fused_kernel<double, PPM, RS, WAVES, FAST, 1>;
+template <bool PPM, int RS, int WAVES, bool FAST, int ZR>
+static hipError_t launch_zr(const FusedArgs<double>& a, int grid, hipStream_t st) {
+  auto k = ctu::ctu_fused_kernel<double, PPM, RS, WAVES, FAST, ZR>;
   const size_t shm = ctu::kLdsBytes(sizeof(double));
   static std::atomic<unsigned long long> lds_set{0};
   const hipError_t e = raise_lds_limit((const void*)k, shm, lds_set);
   if (e != hipSuccess) return e;
   k<<<dim3(grid), dim3(ctu::kThreads), shm, st>>>(a);
   return hipGetLastError();
+}
+
+template <bool PPM, int RS, int WAVES, bool FAST>
+static hipError_t launch_one(const FusedArgs<double>& a, int grid, hipStream_t st) {
+  if (a.zrun != 1) return hipErrorInvalidValue;  // one group (or a part of one) per work item in FP64
+  if (a.zsplit > 1) return launch_zr<PPM, RS, WAVES, FAST, 0>(a, grid, st);
+  return launch_zr<PPM, RS, WAVES, FAST, 1>(a, grid, st);
 }
 
 template <int WAVES, bool FAST>

@@ -47,7 +47,8 @@ constexpr size_t kLdsBytes(size_t elem) { return kLds * elem + 2 * sizeof(unsign
 
 // FAST as in the CTU kernel: van Leer on characteristic variables fixed at
 // compile time.  ZR as in the CTU kernel: groups per work item (tile depth
-// 16 * ZR), ZR > 1 only for a single periodic box without flux output.
+// 16 * ZR), ZR > 1 only for a single periodic box without flux output; ZR = 0
+// a chunk of a group (a.zsplit).
 template <typename T, bool PPM, int RS, int WAVES, int MODE, bool FAST, int ZR>
 __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) {
   constexpr int NT = kThreads;
@@ -87,14 +88,22 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
   // Work items: single groups, or runs of ZR z-consecutive groups of one
   // periodic box, marched through in one pass (the z prologue and the
   // planes beyond each end are paid once per run).
-  constexpr int nzt = 16 * ZR;  // interior planes of an item
+  constexpr bool SPLIT = ZR == 0;
+  constexpr int KR = SPLIT ? 1 : ZR;
   int seg = 0;
-  const GroupOrder order = group_order(a.n_groups / ZR);
+  const GroupOrder order = group_order(SPLIT ? a.n_groups * a.zsplit : a.n_groups / KR);
   for (long long item = order.first; item < order.end; item += order.stride) {
     double dt;
-    const USeg S = find_seg(a, item * ZR, seg, dt);
-    long long lg = item * ZR - S.first;  // the item's first group (local)
-    int gzs = 0;                          // groups between z neighbours
+    long long first = item * KR;  // the item's first group
+    Chunk ck{0, 16 * KR, true, true};
+    if constexpr (SPLIT) {
+      first = uni((int)((unsigned)item / (unsigned)a.zsplit));
+      ck = chunk_of((int)(item - first * a.zsplit), a.zsplit);
+    }
+    const int z0 = SPLIT ? ck.z0 : 0, nzt = SPLIT ? ck.nz : 16 * KR;  // the item's interior planes
+    const USeg S = find_seg(a, first, seg, dt);
+    long long lg = first - S.first;  // (local)
+    int gzs = 0;                     // groups between z neighbours
     if constexpr (ZR > 1) {
       // item -> (column c, run r) of the box; group (r ZR + j) nxy + c
       const int nxy = S.ngx * S.ngy, li = (int)(item - S.first / ZR);
@@ -103,7 +112,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
     }
     const long long grp = S.first + lg;
     T* __restrict__ O = reinterpret_cast<T*>(S.out) + lg * 5 * 4096;
-    T* __restrict__ FO = (ZR == 1 && S.flux) ? reinterpret_cast<T*>(S.flux) + lg * 3 * a.nf * 5 * 256 : nullptr;
+    T* __restrict__ FO = (ZR <= 1 && S.flux) ? reinterpret_cast<T*>(S.flux) + lg * 3 * a.nf * 5 * 256 : nullptr;
     ph.dtdh = (T)(dt / S.dh);
     ph.hdtdh = (T)(0.5 * dt / S.dh);
     // A segment that is no box in a launch that declared boxes only (its
@@ -132,6 +141,10 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
       }
       upd.init(S, lg, col.x, col.y);
     }
+    if constexpr (SPLIT) {
+      src.start_at(z0);
+      if (MODE == 1) upd.start_at(z0);
+    }
     auto wprim = [&](int z) -> V5<T> {
       V5<T> v = src.load(z);
       return MODE == 0 ? prim_of(v, ph) : v;
@@ -152,26 +165,45 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
     V5<T> acc;        // flux differences of the plane being updated, all but its upper z face (lab)
     V5<T> wnext;      // the column's newest z plane, loaded one plane ahead (prims)
     constexpr int zAhead = PPM ? 2 : 1;
-    if (cross) {
+    // A chunk inside the group starts warm planes early: its first iterations
+    // only bring the slope and edge of the z window up to plane -1.  Near the
+    // group's bottom it takes the group's own prologue (PPM: its slopes of
+    // planes -2 and -1 are still needed).
+    constexpr int warm = PPM ? 2 : 0;
+    const bool head = !SPLIT || z0 <= (PPM ? 1 : 0);
+    const int zb = SPLIT ? -z0 : 0;  // the group's plane 0 in a head chunk
+    const int tfirst = head ? zb - 1 : -1 - warm;
+    if (!head) {
+      if (cross) {
+        wa = zprim(PPM ? -3 : -2);
+        wb = zprim(PPM ? -2 : -1);
+        wnext = src.load(tfirst + zAhead);
+        st = em = V5<T>{};
+      }
+    } else if (cross) {
       if (PPM) {
-        V5<T> w3 = zprim(-3), w2 = zprim(-2);
-        wa = zprim(-1);
-        wb = zprim(0);
+        V5<T> w3 = zprim(zb - 3), w2 = zprim(zb - 2);
+        wa = zprim(zb - 1);
+        wb = zprim(zb);
         V5<T> s2 = slope<PPM>(w3, w2, wa, ph);
         st = slope<PPM>(w2, wa, wb, ph);
         em = ppm_edge(w2, wa, s2, st);
       } else {
-        wa = zprim(-2);
-        wb = zprim(-1);
+        wa = zprim(zb - 2);
+        wb = zprim(zb - 1);
       }
-      wnext = src.load(-1 + zAhead);
+      wnext = src.load(zb - 1 + zAhead);
     }
 
-    for (int t = -1; t <= nzt; ++t) {
+    for (int t = tfirst; t <= nzt; ++t) {
+      const bool counted = !SPLIT || ck.counts(t);
+      // The z faces are all that plane t = -1 or nzt of a VL chunk is needed
+      // for, unless its x and y face states are counted (the group's ends).
+      const bool xy = !SPLIT || (t >= -1 && (MODE == 0 || counted));  // uniform
       // ---- A: primitive planes t; z face states of plane t -----------------
       if (cross) {
         if (PPM) {
-          put_plane(pcol, qcol, from_frame<2>(wa));
+          if (xy) put_plane(pcol, qcol, from_frame<2>(wa));
           V5<T> wc = to_frame<2>(MODE == 0 ? prim_of(wnext, ph) : wnext);  // plane t + 2
           wnext = src.load(t + 1 + zAhead <= nzt + zAhead ? t + 1 + zAhead : nzt + zAhead);
           V5<T> sn = slope<PPM>(wa, wb, wc, ph);
@@ -181,17 +213,20 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
           ppm_mono(wa, zfm, zfp);
           wa = wb; wb = wc; st = sn; em = ep;
         } else {
-          put_plane(pcol, qcol, from_frame<2>(wb));
+          if (xy) put_plane(pcol, qcol, from_frame<2>(wb));
           V5<T> wc = to_frame<2>(MODE == 0 ? prim_of(wnext, ph) : wnext);  // plane t + 1
           wnext = src.load(t + 1 + zAhead <= nzt + zAhead ? t + 1 + zAhead : nzt + zAhead);
           V5<T> s0 = slope<PPM>(wa, wb, wc, ph);
           plm_faces(wa, wb, wc, s0, ph, zfm, zfp);
           wa = wb; wb = wc;
         }
-        tally.floors_wave(floor_wave(zfm, ph) + floor_wave(zfp, ph));
-      } else if (col.active) {
+        const unsigned hits = floor_wave(zfm, ph) + floor_wave(zfp, ph);
+        if (counted) tally.floors_wave(hits);
+      } else if (col.active && xy) {
         put_plane(pcol, qcol, wprim(t));
       }
+      if (SPLIT && t < -1) continue;
+      if (xy) {
       __syncthreads();
 
       // ---- B: limited slopes along x and y ---------------------------------
@@ -232,11 +267,13 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
           plm_faces(lds5(pl, kP, c - 1), wc, lds5(pl, kP, c + 1), lds5(ss, kS, (b + 1) * 20 + (aa + 2)), ph, fl,
                     fr);
         }
-        tally.floors_wave(floor_wave(fl, ph) + floor_wave(fr, ph));
+        const unsigned hits = floor_wave(fl, ph) + floor_wave(fr, ph);
+        if (counted) tally.floors_wave(hits);
         sts5(w, kSQ, r, fl);
         sts5(w + 5 * kSQ, kSQ, r, fr);
       }
       __syncthreads();
+      }
 
       // ---- D (MHM): Hancock half step of every cross cell ------------------
       if (MODE == 0) {
@@ -269,7 +306,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
           sts5(wy + 5 * kSQ, kSQ, sqy, correct(yp, dy, ph, nfl));
           zfm = correct(zfm, dz, ph, nfl);
           zfp = correct(zfp, dz, ph, nfl);
-          tally.floors_wave(nfl);
+          if (counted) tally.floors_wave(nfl);
         }
         __syncthreads();
       }
@@ -279,7 +316,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
       if (interior) {
         int nf = 0;
         if (t >= 0) hn = from_frame<2>(riemann<RS>(zhp, zfm, ph, &nf));  // H(t-1/2)
-        tally.fails(nf);
+        if (counted) tally.fails(nf);
         zhp = zfp;
       }
       if (t >= 0 && t < nzt) {
@@ -305,7 +342,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
           // plane t-1 lies in the item's group (t-1)/16, at its z = (t-1)%16
           T* Og = O;
           if constexpr (ZR > 1) Og += (long)((t - 1) >> 4) * gzs * (5 * 4096);
-          const int o = (((t - 1) & 15) * 16 + y) * 16 + x;
+          const int o = (((z0 + t - 1) & 15) * 16 + y) * 16 + x;
 #pragma unroll
           for (int n = 0; n < 5; ++n) gstore(Og + n * 4096, (unsigned)o * (unsigned)sizeof(T), u[n] - ph.dtdh * (acc[n] + hn[n]) + poison);
         }
@@ -316,8 +353,10 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
           for (int n = 0; n < 5; ++n) acc[n] = (fx[n] + gy[n]) - hn[n];  // hn is the lower z face of plane t
         }
         if (FO) {
-          const int f = (t == 0) ? 0 : (t == 16 ? 1 : (t == 8 && a.nf == 3 ? 2 : -1));
-          if (f >= 0) {
+          // z face z0 + t of the group (a chunk's last face is the next one's first)
+          const int p = z0 + t;
+          const int f = (p == 0) ? 0 : (p == 16 ? 1 : (p == 8 && a.nf == 3 ? 2 : -1));
+          if (f >= 0 && (t >= 0 && (t < nzt || p == 16))) {
 #pragma unroll
             for (int n = 0; n < 5; ++n) gstore(FO + ((2 * a.nf + f) * 5 + n) * 256, (unsigned)(y * 16 + x) * (unsigned)sizeof(T), hn[n] + poison);
           }
@@ -330,7 +369,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
           const int fi = f == 0 ? -1 : (f == 1 ? 15 : 7);
           const V5<T> v = from_frame_d(lds5(sF2 + (d ? 5 * kF2 : 0), kF2, s * 17 + fi + 1), d);
 #pragma unroll
-          for (int n = 0; n < 5; ++n) gstore(FO + (((d ? 1 : 0) * a.nf + f) * 5 + n) * 256, (unsigned)(t * 16 + s) * (unsigned)sizeof(T), v[n] + poison);
+          for (int n = 0; n < 5; ++n) gstore(FO + (((d ? 1 : 0) * a.nf + f) * 5 + n) * 256, (unsigned)((z0 + t) * 16 + s) * (unsigned)sizeof(T), v[n] + poison);
         }
       }
     }

@@ -23,6 +23,10 @@ hipError_t launch_zr(const FusedArgs<float>& a, int grid, hipStream_t st) {
 // specialization with two workgroups per CU (zrun_built).
 template <int MODE, bool PPM, int RS, int WAVES, bool FAST>
 hipError_t launch_one(const FusedArgs<float>& a, int grid, hipStream_t st) {
+  if (a.zsplit > 1) {
+    if constexpr (WAVES == 4) return launch_zr<MODE, PPM, RS, WAVES, FAST, 0>(a, grid, st);
+    return hipErrorInvalidValue;
+  }
   if constexpr (WAVES == 4 && FAST && PPM) {
     if (a.zrun == 2) return launch_zr<MODE, PPM, RS, WAVES, FAST, 2>(a, grid, st);
     if (a.zrun == 4) return launch_zr<MODE, PPM, RS, WAVES, FAST, 4>(a, grid, st);

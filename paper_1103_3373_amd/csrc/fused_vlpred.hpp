@@ -69,9 +69,17 @@ __global__ void __launch_bounds__(threads<G>(), 2) vl_predict_kernel(FusedArgs<T
   Phys<T> ph = make_phys(a);
 
   int seg = 0;
-  const GroupOrder order = group_order(a.n_groups);
-  for (long long grp = order.first; grp < order.end; grp += order.stride) {
+  // Work items: chunks of a group's output planes (a.zsplit per group, 1:
+  // whole groups).  A chunk inside the group takes its lowest z face from one
+  // more iteration of the plane loop (the same bits as the chunk below, which
+  // counts it), the group's first chunk from the prologue.
+  const GroupOrder order = group_order(a.n_groups * a.zsplit);
+  for (long long item = order.first; item < order.end; item += order.stride) {
     double dt;
+    const int ns = a.zsplit;
+    const long long grp = ns == 1 ? item : (long long)uni((int)((unsigned)item / (unsigned)ns));
+    const int j = (int)(item - grp * ns);
+    const int zlo = uni(j * Ns / ns) - Gs, zhi = uni((j + 1) * Ns / ns) - Gs;  // output planes zlo .. zhi - 1
     const USeg S = find_seg(a, grp, seg, dt);
     const long long lg = grp - S.first;
     // A box segment beyond the addressing limit: a NaN dt/dh makes every
@@ -84,7 +92,12 @@ __global__ void __launch_bounds__(threads<G>(), 2) vl_predict_kernel(FusedArgs<T
     T* __restrict__ Wo = a.wstar + grp * 5 * NCs;  // the group's half-step array (uniform)
 
     V5<T> u0, w0, u1, w1, hm, unext;
-    if (active) {
+    const int zfirst = j == 0 ? zlo : zlo - 1;
+    if (active && j != 0) {
+      u0 = rd.load(zlo - 1);
+      w0 = prim_of(u0, ph);
+      unext = rd.load(zlo);
+    } else if (active) {
       u0 = rd.load(-Gs - 1);
       w0 = prim_of(u0, ph);
       u1 = rd.load(-Gs);
@@ -94,7 +107,7 @@ __global__ void __launch_bounds__(threads<G>(), 2) vl_predict_kernel(FusedArgs<T
       w0 = w1;
       unext = rd.load(-Gs + 1);
     }
-    for (int z = -Gs; z <= 15 + Gs; ++z) {
+    for (int z = zfirst; z < zhi; ++z) {
       // ---- A: plane z to LDS; z flux above the column's cell.  The column's
       //         plane z+1 was loaded one plane ahead; plane z+2 is requested
       //         now and arrives while phases B and C run --------------------
@@ -102,9 +115,19 @@ __global__ void __launch_bounds__(threads<G>(), 2) vl_predict_kernel(FusedArgs<T
       if (active) {
         sts5(sP, N * N, pc, w0);
         u1 = unext;
-        unext = rd.load(z + 2 <= 16 + Gs ? z + 2 : 16 + Gs);  // clamped on the last plane
+        unext = rd.load(z + 2 <= zhi ? z + 2 : zhi);  // clamped on the last plane
         w1 = prim_of(u1, ph);
-        if (out_col) hp = from_frame<2>(riemann<RS>(to_frame<2>(w0), to_frame<2>(w1), ph, &fails));
+        int nf = 0;
+        if (out_col) hp = from_frame<2>(riemann<RS>(to_frame<2>(w0), to_frame<2>(w1), ph, &nf));
+        if (z >= zlo) fails += nf;
+      }
+      if (z < zlo) {  // uniform
+        if (active) {
+          hm = hp;
+          u0 = u1;
+          w0 = w1;
+        }
+        continue;
       }
       __syncthreads();
       // ---- B: x and y face fluxes of plane z --------------------------------

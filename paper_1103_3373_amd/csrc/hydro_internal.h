@@ -82,6 +82,10 @@ struct FusedArgs {
   // the work items are n_groups / zrun runs (ngz a multiple of zrun).  1
   // everywhere else.
   int zrun;
+  // Small launches: each group's 16 planes are split over zsplit workgroups
+  // (any number from 1 to 16; zrun is 1 then).  1 everywhere else.  The VL
+  // predictor and the solver have their own.
+  int zsplit;
 };
 
 // Tile depths (groups per z-run) built for the fused kernels: 1 always; 2
@@ -98,8 +102,12 @@ struct FusedCfg {
   int grid;          // number of workgroups (persistent)
   int waves;         // register budget variant: minimum waves per SIMD (2 or 4)
   int grid_pred;     // VL predictor workgroups (0 = grid); it marches one group
-                     // at a time whatever the second stage's tile depth
+                     // or chunk at a time whatever the second stage's tile depth
+  int zsplit_pred;   // VL predictor: workgroups per group along z (0 = 1)
 };
+
+// Register variant of the kernels that split groups along z.
+inline int split_waves(bool f64) { return f64 ? 2 : 4; }
 
 bool fused_supported(int scheme, int recon, int riemann, int charlim);
 // Elements of T per group of the VL half-step scratch (0 for other schemes):
