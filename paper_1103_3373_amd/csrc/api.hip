@@ -58,10 +58,17 @@ struct Workspace {
   long long seg_partial_n = 0;
   void* vl = nullptr;  // VL half-step scratch (fused path)
   size_t vl_bytes = 0;
-  double* partial = nullptr;  // reduction partials, kPartials x 6 doubles (a pool slot or own memory)
+  double* partial = nullptr;  // reduction partials, kPartials x 6 doubles, then counters (a pool slot or own memory)
   bool own_partial = false;
+  unsigned next_done = 0;     // counter of the next reduction
 };
 const int kPartialSlots = 64;
+const int kPartials = 1024;  // reduction partials (at most; the number depends on the group count alone)
+// A reduction counts its finished workgroups in one of kDone zeroed sets of
+// counters, taken in turn: reductions captured into graphs keep theirs, so
+// graphs that were captured on one stream and replayed on several share none.
+const int kDone = 32;
+const size_t kPartialBytes = (size_t)kPartials * 6 * sizeof(double) + kDone * hy::kDoneSet * sizeof(unsigned);
 struct DeviceState {
   unsigned long long* diag = nullptr;
   double* partial_pool = nullptr;
@@ -71,7 +78,6 @@ struct DeviceState {
 std::mutex g_mu;
 std::map<int, DeviceState> g_dev;
 
-const int kPartials = 1024;   // reduction partials (fixed: deterministic order)
 const int kPlainGridMax = 512; // plain path: workgroups (each owns 50 N^3 temporaries)
 
 int current_device(int* dev) {
@@ -90,7 +96,8 @@ int device_state(DeviceState** out) {
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(diag)");
     e = hipMemset(d.diag, 0, 2 * sizeof(unsigned long long));
     if (e != hipSuccess) return hip_fail(e, "hipMemset(diag)");
-    e = hipMalloc((void**)&d.partial_pool, (size_t)kPartialSlots * kPartials * 6 * sizeof(double));
+    e = hipMalloc((void**)&d.partial_pool, kPartialSlots * kPartialBytes);
+    if (e == hipSuccess) e = hipMemset(d.partial_pool, 0, kPartialSlots * kPartialBytes);  // counters
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(partial pool)");
   }
   *out = &d;
@@ -129,14 +136,37 @@ int ensure_vl(Workspace& w, size_t bytes) {
 int ensure_partial(DeviceState& d, Workspace& w) {
   if (w.partial) return 0;
   if (d.partial_used < kPartialSlots) {
-    w.partial = d.partial_pool + (size_t)(d.partial_used++) * kPartials * 6;
+    w.partial = reinterpret_cast<double*>(reinterpret_cast<char*>(d.partial_pool) + d.partial_used++ * kPartialBytes);
     return 0;
   }
-  hipError_t e = hipMalloc((void**)&w.partial, (size_t)kPartials * 6 * sizeof(double));
-  if (e != hipSuccess) return hip_fail(e, "hipMalloc(partials)");
+  void* p = nullptr;
+  hipError_t e = hipMalloc(&p, kPartialBytes);
+  if (e == hipSuccess) e = hipMemset(p, 0, kPartialBytes);
+  if (e != hipSuccess) {
+    hipFree(p);
+    return hip_fail(e, "hipMalloc(partials)");
+  }
+  w.partial = static_cast<double*>(p);
   w.own_partial = true;
   return 0;
 }
+// dt and / or sums of n_groups interiors (a null output is not formed).
+int reduce_state(const void* U, int n_groups, double dh, double gamma, double cfl, int flags, double* dt_out,
+                 double* sums_out, hipStream_t st, const char* what) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  DeviceState* ds;
+  if (int rc = device_state(&ds)) return rc;
+  Workspace& w = ds->ws[st];
+  if (int rc = ensure_partial(*ds, w)) return rc;
+  unsigned* done = reinterpret_cast<unsigned*>(w.partial + (size_t)kPartials * 6) + w.next_done++ % kDone * hy::kDoneSet;
+  hipError_t e = (flags & HYDRO_F64) ? hy::launch_reduce((const double*)U, n_groups, dh, gamma, cfl, w.partial,
+                                                         kPartials, done, dt_out, sums_out, st)
+                                     : hy::launch_reduce((const float*)U, n_groups, dh, gamma, cfl, w.partial,
+                                                         kPartials, done, dt_out, sums_out, st);
+  if (e != hipSuccess) return hip_fail(e, what);
+  return 0;
+}
+
 template <typename T>
 hy::Phys<T> make_phys(double dt, double dh, double gamma, int limiter, int flags) {
   hy::Phys<T> p;
@@ -513,19 +543,7 @@ int hydro_cfl_dt(const void* U, int n_groups, double dh, double gamma, double cf
   if (!U || !dt_out) return fail(HYDRO_EINVAL, "null pointer");
   if (!(dh > 0.0) || !(gamma > 1.0) || !(cfl > 0.0)) return fail(HYDRO_EINVAL, "dh, cfl > 0 and gamma > 1 required");
   if (flags & ~kKnownFlags) return fail(HYDRO_EINVAL, "unknown flag bits");
-  hipStream_t st = (hipStream_t)stream;
-  std::lock_guard<std::mutex> lock(g_mu);
-  DeviceState* ds;
-  if (int rc = device_state(&ds)) return rc;
-  Workspace& w = ds->ws[st];
-  if (int rc = ensure_partial(*ds, w)) return rc;
-  hipError_t e = (flags & HYDRO_F64)
-                     ? hy::launch_maxspeed((const double*)U, n_groups, 4096, gamma, w.partial, kPartials, st)
-                     : hy::launch_maxspeed((const float*)U, n_groups, 4096, gamma, w.partial, kPartials, st);
-  if (e != hipSuccess) return hip_fail(e, "max speed");
-  e = hy::launch_dt_finish(w.partial, kPartials, dh, cfl, dt_out, st);
-  if (e != hipSuccess) return hip_fail(e, "dt finish");
-  return 0;
+  return reduce_state(U, n_groups, dh, gamma, cfl, flags, dt_out, nullptr, (hipStream_t)stream, "max speed");
 }
 
 int hydro_cfl_dt_sums(const void* U, int n_groups, double dh, double gamma, double cfl, int flags, double* dt_out,
@@ -536,19 +554,7 @@ int hydro_cfl_dt_sums(const void* U, int n_groups, double dh, double gamma, doub
   if (!(dh > 0.0) || !(gamma > 1.0) || !(cfl > 0.0)) return fail(HYDRO_EINVAL, "dh, cfl > 0 and gamma > 1 required");
   if (flags & ~kKnownFlags) return fail(HYDRO_EINVAL, "unknown flag bits");
   if (overlap(dt_out, sizeof(double), sums_out, 5 * sizeof(double))) return fail(HYDRO_EALIAS, "dt_out overlaps sums_out");
-  hipStream_t st = (hipStream_t)stream;
-  std::lock_guard<std::mutex> lock(g_mu);
-  DeviceState* ds;
-  if (int rc = device_state(&ds)) return rc;
-  Workspace& w = ds->ws[st];
-  if (int rc = ensure_partial(*ds, w)) return rc;
-  hipError_t e = (flags & HYDRO_F64)
-                     ? hy::launch_dtsums((const double*)U, n_groups, dh, gamma, cfl, w.partial, kPartials, dt_out,
-                                         sums_out, st)
-                     : hy::launch_dtsums((const float*)U, n_groups, dh, gamma, cfl, w.partial, kPartials, dt_out,
-                                         sums_out, st);
-  if (e != hipSuccess) return hip_fail(e, "dt and sums");
-  return 0;
+  return reduce_state(U, n_groups, dh, gamma, cfl, flags, dt_out, sums_out, (hipStream_t)stream, "dt and sums");
 }
 
 int hydro_cfl_dt_batch(const struct hydro_seg* segs, int n_segs, long long n_groups_total, double gamma, double cfl,
@@ -608,17 +614,7 @@ int hydro_conserved_sums(const void* U, int n_groups, double dh, int flags, doub
   if (!U || !sums_out) return fail(HYDRO_EINVAL, "null pointer");
   if (!(dh > 0.0)) return fail(HYDRO_EINVAL, "dh must be positive");
   if (flags & ~kKnownFlags) return fail(HYDRO_EINVAL, "unknown flag bits");
-  hipStream_t st = (hipStream_t)stream;
-  std::lock_guard<std::mutex> lock(g_mu);
-  DeviceState* ds;
-  if (int rc = device_state(&ds)) return rc;
-  Workspace& w = ds->ws[st];
-  if (int rc = ensure_partial(*ds, w)) return rc;
-  hipError_t e = (flags & HYDRO_F64)
-                     ? hy::launch_sums((const double*)U, n_groups, 4096, dh, w.partial, kPartials, sums_out, st)
-                     : hy::launch_sums((const float*)U, n_groups, 4096, dh, w.partial, kPartials, sums_out, st);
-  if (e != hipSuccess) return hip_fail(e, "conserved sums");
-  return 0;
+  return reduce_state(U, n_groups, dh, 2.0, 1.0, flags, nullptr, sums_out, (hipStream_t)stream, "conserved sums");
 }
 
 int hydro_fill_ghosts_periodic(const void* box, int nx, int ny, int nz, int g, int flags, void* groups_out,

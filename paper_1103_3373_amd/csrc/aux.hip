@@ -2,11 +2,13 @@
 //  * preparation step (paper Sec. 4.2): periodic ghost fill of patch groups
 //    from a resident box, and trilinear fill of AMR-shaped groups from a
 //    coarse field (spatial interpolation at coarse-fine boundaries);
-//  * FP64 CFL time step: max signal speed per block (wave64 shuffles), then a
-//    single-block finish, dt = cfl * dh / max (max is order-free, so the
-//    result is deterministic and equals a serial evaluation bit for bit);
-//  * FP64 conserved sums with a fixed two-level reduction order.
+//  * FP64 CFL time step, dt = cfl * dh / max (max is order-free, so the result
+//    is deterministic and equals a serial evaluation bit for bit), and FP64
+//    conserved sums with a fixed reduction order, in one launch; the time steps
+//    of a segment table in two.
 #include <limits.h>
+
+#include <type_traits>
 
 #include "hydro_internal.h"
 
@@ -656,45 +658,69 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// U: n_blocks blocks of [5][4096]; one partial max per workgroup.  The
-// per-cell expression is written out in a fixed order with contraction off.
-template <typename T>
-__global__ void __launch_bounds__(256) maxspeed_kernel(const T* __restrict__ U, long long n_blocks, double gamma,
-                                                       double* __restrict__ partial) {
-#pragma clang fp contract(off)
-  __shared__ double red[4];
-  double m = 0.0;
-  const long long total = n_blocks << 12;
-#pragma unroll 4
-  for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total;
-       t += (long long)gridDim.x * blockDim.x) {
-    const T* u = U + ((t >> 12) * 5 << 12) + (t & 4095);
-    const double rho = (double)u[0];
-    const double mx = (double)u[4096], my = (double)u[2 * 4096], mz = (double)u[3 * 4096];
-    const double vx = mx / rho, vy = my / rho, vz = mz / rho;
-    const double ke = 0.5 * (mx * vx + my * vy + mz * vz);
-    const double p = (gamma - 1.0) * ((double)u[4 * 4096] - ke);
-    const double cs = __builtin_sqrt(gamma * p / rho);
-    double av = __builtin_fabs(vx);
-    if (__builtin_fabs(vy) > av) av = __builtin_fabs(vy);
-    if (__builtin_fabs(vz) > av) av = __builtin_fabs(vz);
-    const double s = av + cs;
-    m = s > m ? s : m;
+// Four consecutive cells of one variable.  WIDE: 16-byte loads (the array is
+// 16-byte aligned; groups and variables are whole multiples of that).
+template <typename T, bool WIDE> __device__ __forceinline__ void load4(const T* p, T (&v)[4]) {
+  if constexpr (WIDE && sizeof(T) == 4) {
+    const float4 q = *reinterpret_cast<const float4*>(p);
+    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+  } else if constexpr (WIDE) {
+    const double2 a = reinterpret_cast<const double2*>(p)[0], b = reinterpret_cast<const double2*>(p)[1];
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = p[k];
   }
-  m = wave_max(m);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) partial[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+}
+
+// Quotients by one divisor b, correctly rounded like the compiler's division:
+// the same reciprocal refinement and residual step, the refinement done once
+// and without the exponent scaling, which is the identity for operands in the
+// range of values upcast from float (and their products and differences).
+struct SharedDiv {
+  double b, r;
+  __device__ __forceinline__ explicit SharedDiv(double d) : b(d), r(__builtin_amdgcn_rcp(d)) {
+    r = __builtin_fma(r, __builtin_fma(-b, r, 1.0), r);
+    r = __builtin_fma(r, __builtin_fma(-b, r, 1.0), r);
+  }
+  __device__ __forceinline__ double operator()(double a) const {
+    const double q = a * r;
+    return __builtin_amdgcn_div_fixup(__builtin_fma(__builtin_fma(-b, q, a), r, q), b, a);  // zero, inf and NaN
+  }
+};
+struct IeeeDiv {
+  double b;
+  __device__ __forceinline__ explicit IeeeDiv(double d) : b(d) {}
+  __device__ __forceinline__ double operator()(double a) const { return a / b; }
+};
+
+// max_d |v_d| + c of a conserved cell of type T, in the order and rounding of
+// a serial IEEE evaluation.
+template <typename T> __device__ __forceinline__ double signal_speed(const double c[5], double gamma) {
+#pragma clang fp contract(off)
+  using Div = typename std::conditional<sizeof(T) == 4, SharedDiv, IeeeDiv>::type;
+  const Div over_rho(c[0]);
+  const double mx = c[1], my = c[2], mz = c[3];
+  const double vx = over_rho(mx), vy = over_rho(my), vz = over_rho(mz);
+  const double ke = 0.5 * (mx * vx + my * vy + mz * vz);
+  const double p = (gamma - 1.0) * (c[4] - ke);
+  const double cs = __builtin_sqrt(over_rho(gamma * p));
+  double av = __builtin_fabs(vx);
+  if (__builtin_fabs(vy) > av) av = __builtin_fabs(vy);
+  if (__builtin_fabs(vz) > av) av = __builtin_fabs(vz);
+  return av + cs;
 }
 
 // Batched time step: one workgroup per group of a segment table computes the
-// group's maximum signal speed (same expression as above); one workgroup per
-// segment then writes dt = cfl * dh / max to the segment's dt pointer.
+// group's maximum signal speed (same expression as above), four cells a
+// thread: the launch is short and bound by latency, so all of a group's loads
+// are in flight at once (520 FP32 groups, finish included: 13.6 us, 18.0 with
+// 256 threads that took 16 cells one after another).  One workgroup per segment then
+// writes dt = cfl * dh / max to the segment's dt pointer.
 template <typename T>
-__global__ void __launch_bounds__(256) seg_maxspeed_kernel(const Seg* __restrict__ segs, int n_segs, double gamma,
-                                                           double* __restrict__ partial) {
-#pragma clang fp contract(off)
-  __shared__ double red[4];
+__global__ void __launch_bounds__(1024) seg_maxspeed_kernel(const Seg* __restrict__ segs, int n_segs, double gamma,
+                                                            double* __restrict__ partial) {
+  __shared__ double red[16];
   const long long gidx = blockIdx.x;
   int lo = 0, hi = n_segs - 1;  // last segment with first <= gidx
   while (lo < hi) {
@@ -703,26 +729,29 @@ __global__ void __launch_bounds__(256) seg_maxspeed_kernel(const Seg* __restrict
     else hi = mid - 1;
   }
   const Seg& S = segs[lo];
-  const T* U = reinterpret_cast<const T*>(S.out) + (gidx - S.first) * 5 * 4096;
+  const T* u = reinterpret_cast<const T*>(S.out) + (gidx - S.first) * 5 * 4096 + threadIdx.x * 4;
+  T v[5][4];
+  if ((uintptr_t)S.out % 16 == 0) {  // uniform
+#pragma unroll
+    for (int n = 0; n < 5; ++n) load4<T, true>(u + n * 4096, v[n]);
+  } else {
+#pragma unroll
+    for (int n = 0; n < 5; ++n) load4<T, false>(u + n * 4096, v[n]);
+  }
   double m = 0.0;
-  for (int q = threadIdx.x; q < 4096; q += blockDim.x) {
-    const T* u = U + q;
-    const double rho = (double)u[0];
-    const double mx = (double)u[4096], my = (double)u[2 * 4096], mz = (double)u[3 * 4096];
-    const double vx = mx / rho, vy = my / rho, vz = mz / rho;
-    const double ke = 0.5 * (mx * vx + my * vy + mz * vz);
-    const double p = (gamma - 1.0) * ((double)u[4 * 4096] - ke);
-    const double cs = __builtin_sqrt(gamma * p / rho);
-    double av = __builtin_fabs(vx);
-    if (__builtin_fabs(vy) > av) av = __builtin_fabs(vy);
-    if (__builtin_fabs(vz) > av) av = __builtin_fabs(vz);
-    const double sp = av + cs;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double c[5] = {(double)v[0][k], (double)v[1][k], (double)v[2][k], (double)v[3][k], (double)v[4][k]};
+    const double sp = signal_speed<T>(c, gamma);
     m = sp > m ? sp : m;
   }
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0) partial[gidx] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  if (threadIdx.x < 64) {
+    m = wave_max(threadIdx.x < 16 ? red[threadIdx.x] : 0.0);
+    if (threadIdx.x == 0) partial[gidx] = m;
+  }
 }
 
 __global__ void __launch_bounds__(256) seg_dt_finish_kernel(const Seg* __restrict__ segs,
@@ -744,204 +773,154 @@ __global__ void __launch_bounds__(256) seg_dt_finish_kernel(const Seg* __restric
 hipError_t launch_seg_dt(const Seg* segs, int n_segs, long long n_groups, double gamma, double cfl, int f64,
                          double* partial, hipStream_t st) {
   if (n_groups > 2147483647LL) return hipErrorInvalidValue;
-  if (f64) seg_maxspeed_kernel<double><<<dim3((unsigned)n_groups), dim3(256), 0, st>>>(segs, n_segs, gamma, partial);
-  else seg_maxspeed_kernel<float><<<dim3((unsigned)n_groups), dim3(256), 0, st>>>(segs, n_segs, gamma, partial);
+  if (f64) seg_maxspeed_kernel<double><<<dim3((unsigned)n_groups), dim3(1024), 0, st>>>(segs, n_segs, gamma, partial);
+  else seg_maxspeed_kernel<float><<<dim3((unsigned)n_groups), dim3(1024), 0, st>>>(segs, n_segs, gamma, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   seg_dt_finish_kernel<<<dim3(n_segs), dim3(256), 0, st>>>(segs, partial, cfl);
   return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) dt_finish_kernel(const double* __restrict__ partial, int n, double dh,
-                                                        double cfl, double* __restrict__ dt_out) {
-#pragma clang fp contract(off)
-  __shared__ double red[4];
-  double m = 0.0;
-  for (int t = threadIdx.x; t < n; t += blockDim.x) m = fmax(m, partial[t]);
-  m = wave_max(m);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const double mx = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-    dt_out[0] = cfl * dh / mx;
-  }
-}
-
-template <typename T>
-hipError_t launch_maxspeed(const T* U, long long n_blocks, long long cells, double gamma, double* partial,
-                           int n_partial, hipStream_t st) {
-  if (cells != 4096) return hipErrorInvalidValue;
-  maxspeed_kernel<T><<<dim3(n_partial), dim3(256), 0, st>>>(U, n_blocks, gamma, partial);
-  return hipGetLastError();
-}
-template hipError_t launch_maxspeed<float>(const float*, long long, long long, double, double*, int, hipStream_t);
-template hipError_t launch_maxspeed<double>(const double*, long long, long long, double, double*, int, hipStream_t);
-
-hipError_t launch_dt_finish(const double* partial, int n_partial, double dh, double cfl, double* dt_out,
-                            hipStream_t st) {
-  dt_finish_kernel<<<dim3(1), dim3(256), 0, st>>>(partial, n_partial, dh, cfl, dt_out);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
-// FP64 conserved sums.  Workgroup w sums a fixed contiguous slice of cells
-// (lane-strided, then a fixed shuffle tree); a single workgroup then adds the
-// partials in index order.  The order depends only on n_partial, never on
-// timing, so repeated calls are bitwise identical.
+// Time step and conserved sums of a whole state, one launch.  A workgroup
+// takes a contiguous slice of 1,024-cell chunks (four consecutive cells a
+// thread and chunk, lane order, then fixed shuffle trees) and stores its
+// partial results; the workgroup that finishes last reduces the partials, in a
+// fixed order, and writes the results.  The slices depend on the number of
+// groups alone, so repeated calls are bitwise identical, and the time step and
+// the sums are the same whether they are asked for together or apart.
+//
+// Small states are bound by launches (12.2 us with a second launch for the
+// finish and scalar loads, 6.6 us now, at 8 groups), large ones by reading the
+// state once (4,096 FP32 groups: 81 -> 63 us, 5.4 TB/s; 512: 18.4 -> 13.4).
+// In between, the workgroups' arrivals count: up to 512 of them are as fast as
+// 1,024 below 2,048 groups (512 groups 13.4 against 14.2 us) and slower from
+// there (4,096 groups 66 against 63 us).
+//
+// The partials pass between workgroups on different XCDs, whose L2 caches are
+// not coherent for plain accesses: they are stored and loaded as device-scope
+// atomics, and a workgroup counts itself as done only after its stores have
+// been acknowledged.  The counters wrap to zero by themselves.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256) sums_kernel(const T* __restrict__ U, long long n_blocks,
-                                                   double* __restrict__ partial) {
-  __shared__ double red[5][4];
-  const long long total = n_blocks << 12;
-  const long long per = (total + gridDim.x - 1) / gridDim.x;
-  const long long lo = blockIdx.x * per, hi = min(total, lo + per);
-  double s[5] = {0, 0, 0, 0, 0};
-  for (long long t = lo + threadIdx.x; t < hi; t += blockDim.x) {
-    const T* u = U + ((t >> 12) * 5 << 12) + (t & 4095);
-#pragma unroll
-    for (int n = 0; n < 5; ++n) s[n] += (double)u[n * 4096];
-  }
-#pragma unroll
-  for (int n = 0; n < 5; ++n) {
-    double v = wave_sum(s[n]);
-    if ((threadIdx.x & 63) == 0) red[n][threadIdx.x >> 6] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x < 5) {
-    const int n = threadIdx.x;
-    partial[(long long)blockIdx.x * 5 + n] = (red[n][0] + red[n][1]) + (red[n][2] + red[n][3]);
-  }
-}
+enum { kRedDt = 1, kRedSums = 2 };
 
-// Fixed-order finish: thread q adds partials q, q+256, ... in index order,
-// then a fixed shuffle tree and a fixed cross-wave sum.
-__global__ void __launch_bounds__(256) sums_finish_kernel(const double* __restrict__ partial, int n, double vol,
-                                                         double* __restrict__ out) {
-  __shared__ double red[5][4];
-#pragma unroll
-  for (int v = 0; v < 5; ++v) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < n; b += blockDim.x) s += partial[(long long)b * 5 + v];
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) red[v][threadIdx.x >> 6] = s;
-  }
-  __syncthreads();
-  if (threadIdx.x < 5) {
-    const int v = threadIdx.x;
-    out[v] = ((red[v][0] + red[v][1]) + (red[v][2] + red[v][3])) * vol;
-  }
-}
-
-template <typename T>
-hipError_t launch_sums(const T* U, long long n_blocks, long long cells, double dh, double* partial, int n_partial,
-                       double* sums_out, hipStream_t st) {
-  if (cells != 4096) return hipErrorInvalidValue;
-  sums_kernel<T><<<dim3(n_partial), dim3(256), 0, st>>>(U, n_blocks, partial);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  sums_finish_kernel<<<dim3(1), dim3(256), 0, st>>>(partial, n_partial, dh * dh * dh, sums_out);
-  return hipGetLastError();
-}
-template hipError_t launch_sums<float>(const float*, long long, long long, double, double*, int, double*, hipStream_t);
-template hipError_t launch_sums<double>(const double*, long long, long long, double, double*, int, double*,
-                                        hipStream_t);
-
-// ---------------------------------------------------------------------------
-// Time step and conserved sums in one pass over the state.  Workgroup w takes
-// the same contiguous slice, lane order and shuffle trees as sums_kernel, and
-// evaluates the signal speed with the same expression as maxspeed_kernel on
-// the same cells; the finish repeats dt_finish_kernel and sums_finish_kernel.
-// Both results are therefore bit-identical to the two separate reductions,
-// while the state is read once.
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256) dtsums_kernel(const T* __restrict__ U, long long n_blocks, double gamma,
-                                                     double* __restrict__ partial) {
+template <typename T, int MODE, bool WIDE>
+__global__ void __launch_bounds__(256) reduce_kernel(const T* __restrict__ U, long long n_chunks, long long per,
+                                                     double gamma, double cdh, double vol, double* partial,
+                                                     unsigned* done, double* __restrict__ dt_out,
+                                                     double* __restrict__ sums_out) {
 #pragma clang fp contract(off)
   __shared__ double red[6][4];
-  const long long total = n_blocks << 12;
-  const long long per = (total + gridDim.x - 1) / gridDim.x;
-  const long long lo = blockIdx.x * per, hi = min(total, lo + per);
-  double s[5] = {0, 0, 0, 0, 0};
-  double m = 0.0;
-  // Unrolled so that the FP64 division chains of several cells overlap; the
-  // sums still take the cells of a lane in order.
-#pragma unroll 4
-  for (long long t = lo + threadIdx.x; t < hi; t += blockDim.x) {
-    const T* u = U + ((t >> 12) * 5 << 12) + (t & 4095);
-    double c[5];
+  __shared__ int last;
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const long long lo = blockIdx.x * per, hi = lo + per < n_chunks ? lo + per : n_chunks;
+  double s[5] = {0, 0, 0, 0, 0}, m = 0.0;
+#pragma unroll 2
+  for (long long c = lo; c < hi; ++c) {
+    const T* u = U + (c >> 2) * (5 * 4096) + (c & 3) * 1024 + tid * 4;
+    T v[5][4];
 #pragma unroll
-    for (int n = 0; n < 5; ++n) c[n] = (double)u[n * 4096];
+    for (int n = 0; n < 5; ++n) load4<T, WIDE>(u + n * 4096, v[n]);
 #pragma unroll
-    for (int n = 0; n < 5; ++n) s[n] += c[n];
-    const double rho = c[0];
-    const double mx = c[1], my = c[2], mz = c[3];
-    const double vx = mx / rho, vy = my / rho, vz = mz / rho;
-    const double ke = 0.5 * (mx * vx + my * vy + mz * vz);
-    const double p = (gamma - 1.0) * (c[4] - ke);
-    const double cs = __builtin_sqrt(gamma * p / rho);
-    double av = __builtin_fabs(vx);
-    if (__builtin_fabs(vy) > av) av = __builtin_fabs(vy);
-    if (__builtin_fabs(vz) > av) av = __builtin_fabs(vz);
-    const double sp = av + cs;
-    m = sp > m ? sp : m;
+    for (int k = 0; k < 4; ++k) {
+      const double q[5] = {(double)v[0][k], (double)v[1][k], (double)v[2][k], (double)v[3][k], (double)v[4][k]};
+      if constexpr (MODE & kRedSums) {
+#pragma unroll
+        for (int n = 0; n < 5; ++n) s[n] += q[n];
+      }
+      if constexpr (MODE & kRedDt) {
+        const double sp = signal_speed<T>(q, gamma);
+        m = sp > m ? sp : m;
+      }
+    }
   }
+  // Per-workgroup results: partial[n * P + b], n = 0..4 the sums, 5 the maximum.
+  const int P = gridDim.x;
+  auto block_reduce = [&]() {
+    if constexpr (MODE & kRedSums) {
 #pragma unroll
-  for (int n = 0; n < 5; ++n) {
-    double v = wave_sum(s[n]);
-    if ((threadIdx.x & 63) == 0) red[n][threadIdx.x >> 6] = v;
+      for (int n = 0; n < 5; ++n) {
+        const double v = wave_sum(s[n]);
+        if ((tid & 63) == 0) red[n][wave] = v;
+      }
+    }
+    if constexpr (MODE & kRedDt) {
+      m = wave_max(m);
+      if ((tid & 63) == 0) red[5][wave] = m;
+    }
+    __syncthreads();
+  };
+  constexpr int n0 = MODE & kRedSums ? 0 : 5, n1 = MODE & kRedDt ? 6 : 5;
+  auto block_value = [&](int n) -> double {
+    return n < 5 ? (red[n][0] + red[n][1]) + (red[n][2] + red[n][3])
+                 : fmax(fmax(red[n][0], red[n][1]), fmax(red[n][2], red[n][3]));
+  };
+  block_reduce();
+  if (wave == 0) {
+    if (tid >= n0 && tid < n1)
+      __hip_atomic_store(&partial[(long long)tid * P + blockIdx.x], block_value(tid), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's stores have reached the device's memory
+    if (tid == 0) {
+      // Workgroup b counts in counter b mod 16, the last of each in the main
+      // one: increments of one address take about 10 ns each, one after another.
+      const unsigned k = blockIdx.x % kDoneLeaves, n = (unsigned)P / kDoneLeaves + (k < (unsigned)P % kDoneLeaves);
+      const unsigned leaves = (unsigned)P < kDoneLeaves ? (unsigned)P : kDoneLeaves;
+      last = atomicInc(done + (k + 1) * kDoneStride, n - 1u) == n - 1u && atomicInc(done, leaves - 1u) == leaves - 1u;
+    }
   }
-  m = wave_max(m);
-  if ((threadIdx.x & 63) == 0) red[5][threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x < 5) {
-    const int n = threadIdx.x;
-    partial[(long long)blockIdx.x * 5 + n] = (red[n][0] + red[n][1]) + (red[n][2] + red[n][3]);
-  } else if (threadIdx.x == 5) {
-    partial[(long long)gridDim.x * 5 + blockIdx.x] = fmax(fmax(red[5][0], red[5][1]), fmax(red[5][2], red[5][3]));
+  if (!last) return;
+  m = 0.0;
+#pragma unroll
+  for (int n = 0; n < 5; ++n) s[n] = 0.0;
+  for (int b = tid; b < P; b += 256) {
+    double v[6];
+#pragma unroll
+    for (int n = n0; n < n1; ++n)
+      v[n] = __hip_atomic_load(&partial[(long long)n * P + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (MODE & kRedSums) {
+#pragma unroll
+      for (int n = 0; n < 5; ++n) s[n] += v[n];
+    }
+    if constexpr (MODE & kRedDt) m = fmax(m, v[5]);
+  }
+  block_reduce();
+  if (tid >= n0 && tid < n1) {
+    const double v = block_value(tid);
+    if (tid < 5) sums_out[tid] = v * vol;
+    else dt_out[0] = cdh / v;
   }
 }
 
-__global__ void __launch_bounds__(256) dtsums_finish_kernel(const double* __restrict__ partial, int n, double dh,
-                                                           double cfl, double* __restrict__ dt_out,
-                                                           double* __restrict__ sums_out) {
-#pragma clang fp contract(off)
-  __shared__ double red[6][4];
-#pragma unroll
-  for (int v = 0; v < 5; ++v) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < n; b += blockDim.x) s += partial[(long long)b * 5 + v];
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) red[v][threadIdx.x >> 6] = s;
-  }
-  double m = 0.0;
-  for (int t = threadIdx.x; t < n; t += blockDim.x) m = fmax(m, partial[(long long)n * 5 + t]);
-  m = wave_max(m);
-  if ((threadIdx.x & 63) == 0) red[5][threadIdx.x >> 6] = m;
-  __syncthreads();
-  const double vol = dh * dh * dh;
-  if (threadIdx.x < 5) {
-    const int v = threadIdx.x;
-    sums_out[v] = ((red[v][0] + red[v][1]) + (red[v][2] + red[v][3])) * vol;
-  } else if (threadIdx.x == 5) {
-    const double mx = fmax(fmax(red[5][0], red[5][1]), fmax(red[5][2], red[5][3]));
-    dt_out[0] = cfl * dh / mx;
-  }
+template <typename T, int MODE>
+static hipError_t launch_reduce_mode(const T* U, long long n_groups, double dh, double gamma, double cfl,
+                                     double* partial, int max_partial, unsigned* done, double* dt_out,
+                                     double* sums_out, hipStream_t st) {
+  const long long n_chunks = 4 * n_groups;
+  if (n_groups < 2048) max_partial /= 2;
+  const long long per = (n_chunks + max_partial - 1) / max_partial > 0 ? (n_chunks + max_partial - 1) / max_partial : 1;
+  const long long P = (n_chunks + per - 1) / per > 0 ? (n_chunks + per - 1) / per : 1;  // no groups: one workgroup
+  auto k = (uintptr_t)U % 16 == 0 ? reduce_kernel<T, MODE, true> : reduce_kernel<T, MODE, false>;
+  k<<<dim3((unsigned)P), dim3(256), 0, st>>>(U, n_chunks, per, gamma, cfl * dh, dh * dh * dh, partial, done, dt_out,
+                                            sums_out);
+  return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_dtsums(const T* U, long long n_blocks, double dh, double gamma, double cfl, double* partial,
-                         int n_partial, double* dt_out, double* sums_out, hipStream_t st) {
-  dtsums_kernel<T><<<dim3(n_partial), dim3(256), 0, st>>>(U, n_blocks, gamma, partial);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  dtsums_finish_kernel<<<dim3(1), dim3(256), 0, st>>>(partial, n_partial, dh, cfl, dt_out, sums_out);
-  return hipGetLastError();
+hipError_t launch_reduce(const T* U, long long n_groups, double dh, double gamma, double cfl, double* partial,
+                         int max_partial, unsigned* done, double* dt_out, double* sums_out, hipStream_t st) {
+  if (dt_out && sums_out)
+    return launch_reduce_mode<T, kRedDt | kRedSums>(U, n_groups, dh, gamma, cfl, partial, max_partial, done, dt_out,
+                                                    sums_out, st);
+  if (dt_out)
+    return launch_reduce_mode<T, kRedDt>(U, n_groups, dh, gamma, cfl, partial, max_partial, done, dt_out, sums_out, st);
+  return launch_reduce_mode<T, kRedSums>(U, n_groups, dh, gamma, cfl, partial, max_partial, done, dt_out, sums_out, st);
 }
-template hipError_t launch_dtsums<float>(const float*, long long, double, double, double, double*, int, double*,
-                                         double*, hipStream_t);
-template hipError_t launch_dtsums<double>(const double*, long long, double, double, double, double*, int, double*,
-                                          double*, hipStream_t);
+template hipError_t launch_reduce<float>(const float*, long long, double, double, double, double*, int, unsigned*,
+                                         double*, double*, hipStream_t);
+template hipError_t launch_reduce<double>(const double*, long long, double, double, double, double*, int, unsigned*,
+                                          double*, double*, hipStream_t);
 
 }  // namespace hy

@@ -136,18 +136,16 @@ hipError_t launch_fill_amr(const T* fine, const int* layout, int n_groups, const
 template <typename T>
 hipError_t launch_fill_interp(const T* coarse, int cn, const int* layout, long long n_groups, int g, double base_dh,
                               T* out, hipStream_t st);
-template <typename T>
-hipError_t launch_maxspeed(const T* U, long long n_blocks, long long cells, double gamma, double* partial,
-                           int n_partial, hipStream_t st);
 hipError_t launch_seg_dt(const Seg* segs, int n_segs, long long n_groups, double gamma, double cfl, int f64,
                          double* partial, hipStream_t st);
-hipError_t launch_dt_finish(const double* partial, int n_partial, double dh, double cfl, double* dt_out,
-                            hipStream_t st);
+// dt (dt_out, may be null) and conserved sums (sums_out, may be null) of
+// n_groups interiors.  partial: 6 max_partial doubles; done: a zeroed set of
+// counters that no other launch in flight uses (zero again afterwards): a main
+// one and kDoneLeaves, each on a cache line of its own.
+constexpr unsigned kDoneLeaves = 16, kDoneStride = 16;
+constexpr unsigned kDoneSet = (kDoneLeaves + 1) * kDoneStride;
 template <typename T>
-hipError_t launch_sums(const T* U, long long n_blocks, long long cells, double dh, double* partial, int n_partial,
-                       double* sums_out, hipStream_t st);
-template <typename T>
-hipError_t launch_dtsums(const T* U, long long n_blocks, double dh, double gamma, double cfl, double* partial,
-                         int n_partial, double* dt_out, double* sums_out, hipStream_t st);
+hipError_t launch_reduce(const T* U, long long n_groups, double dh, double gamma, double cfl, double* partial,
+                         int max_partial, unsigned* done, double* dt_out, double* sums_out, hipStream_t st);
 
 }  // namespace hy
