@@ -54,11 +54,11 @@ enum hydro_scheme { HYDRO_MHM = 0, HYDRO_VL = 1, HYDRO_CTU = 2 };
 /* Reconstruction (Sec. 2). */
 enum hydro_recon { HYDRO_PLM = 0, HYDRO_PPM = 1 };
 /* Riemann solvers (Sec. 2).  The exact solver (Newton iteration on the
- * star pressure, then sampling on the face) runs on the plain path only:
- * hydro_solve_groups takes that path for it, and the fused-only calls
- * (hydro_solve_batch, hydro_step_box, hydro_autotune) return
+ * star pressure, then sampling on the face) is for hydro_solve_groups: the
+ * other calls (hydro_solve_batch, hydro_step_box, hydro_autotune) return
  * HYDRO_EUNSUPPORTED.  With HYDRO_EXACT the first diagnostic counter counts
- * faces that generate vacuum or do not converge. */
+ * solves that generate vacuum or do not converge (HYDRO_PLAIN solves more
+ * ghost faces than the fused path). */
 enum hydro_riemann { HYDRO_ROE = 0, HYDRO_HLLC = 1, HYDRO_HLLE = 2, HYDRO_EXACT = 3 };
 /* Slope limiters (Sec. 2).  The hybrid limiter is the van Leer slope bounded
  * by the generalized minmod slope; theta = 1.5 for both. */

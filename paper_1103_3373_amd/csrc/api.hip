@@ -324,6 +324,8 @@ int run_fused(const hy::Seg* segs_dev, int n_segs, long long n_groups, int g, in
   a.g = g;
   a.nf = (flags & HYDRO_FLUX_MID) ? 3 : 2;
   a.gamma = (T)gamma;
+  a.gm1 = (T)(gamma - 1.0);
+  a.inv_gm1 = (T)(1.0 / (gamma - 1.0));
   a.theta = (T)1.5;
   a.floor = (T)1e-10;
   a.limiter = limiter;
@@ -415,10 +417,8 @@ int hydro_solve_groups(const void* in, void* out, void* flux_out, int n_groups, 
   if (int rc = device_state(&ds)) return rc;
   Workspace& w = ds->ws[st];
 
-  // The exact solver (riemann 3) and the Roe -> exact fallback run on the
-  // plain path only.
-  const bool plain = (flags & (HYDRO_PLAIN | HYDRO_ROE_FB_EXACT)) ||
-                     !hy::fused_supported(scheme, reconstruction, riemann, (flags & HYDRO_CHAR) ? 1 : 0);
+  // The Roe -> exact fallback runs on the plain path only.
+  const bool plain = (flags & (HYDRO_PLAIN | HYDRO_ROE_FB_EXACT)) != 0;
   if (plain) {
     int grid = n_groups < kPlainGridMax ? n_groups : kPlainGridMax;
     const long stride = 50L * N * N * N;

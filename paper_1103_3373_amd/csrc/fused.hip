@@ -11,6 +11,8 @@ hipError_t launch_muscl_f32(const FusedArgs<float>& a, int mode, int recon, int 
                             hipStream_t st);
 hipError_t launch_muscl_f64(const FusedArgs<double>& a, int mode, int recon, int riemann, const FusedCfg& cfg,
                             hipStream_t st);
+hipError_t launch_exact_f32(const FusedArgs<float>& a, int scheme, int recon, const FusedCfg& cfg, hipStream_t st);
+hipError_t launch_exact_f64(const FusedArgs<double>& a, int scheme, int recon, const FusedCfg& cfg, hipStream_t st);
 hipError_t launch_vlpred_f32(const FusedArgs<float>& a, int recon, int riemann, int grid, hipStream_t st);
 hipError_t launch_vlpred_f64(const FusedArgs<double>& a, int recon, int riemann, int grid, hipStream_t st);
 
@@ -47,10 +49,12 @@ static hipError_t dispatch(const FusedArgs<T>& a, int scheme, int recon, int rie
 
 hipError_t launch_fused(const FusedArgs<float>& a, int scheme, int recon, int riemann, const FusedCfg& cfg,
                         hipStream_t st) {
+  if (riemann == 3) return launch_exact_f32(a, scheme, recon, cfg, st);
   return dispatch<float>(a, scheme, recon, riemann, cfg, st, launch_ctu_f32, launch_muscl_f32, launch_vlpred_f32);
 }
 hipError_t launch_fused(const FusedArgs<double>& a, int scheme, int recon, int riemann, const FusedCfg& cfg,
                         hipStream_t st) {
+  if (riemann == 3) return launch_exact_f64(a, scheme, recon, cfg, st);
   return dispatch<double>(a, scheme, recon, riemann, cfg, st, launch_ctu_f64, launch_muscl_f64, launch_vlpred_f64);
 }
 int fused_block_threads() { return 512; }

@@ -116,12 +116,15 @@ HY_DEV GroupOrder group_order(long long n_groups) {
   return GroupOrder{lo + b / 8, P / 8, hi};
 }
 
-// Per-launch physics constants (dt/dh set per group from its segment).
-template <typename T> HY_DEV Phys<T> make_phys(const FusedArgs<T>& a) {
+// Per-launch physics constants (dt/dh set per group from its segment).  With
+// the exact solver (RS 3) gamma - 1 is the one rounded from double, as the
+// paper-style kernel has it: its powers 2/(gamma - 1) of a negative fan base
+// (vacuum) are real for a whole exponent only.
+template <int RS, typename T> HY_DEV Phys<T> make_phys(const FusedArgs<T>& a) {
   Phys<T> ph;
   ph.gamma = a.gamma;
-  ph.gm1 = a.gamma - T(1);
-  ph.inv_gm1 = T(1) / ph.gm1;
+  ph.gm1 = RS == 3 ? a.gm1 : a.gamma - T(1);
+  ph.inv_gm1 = RS == 3 ? a.inv_gm1 : T(1) / ph.gm1;
   ph.theta = a.theta;
   ph.floor = a.floor;
   ph.limiter = a.limiter;

@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
   if (tid < 2) tally.c[tid] = 0u;
   __syncthreads();
 
-  Phys<T> ph = make_phys(a);
+  Phys<T> ph = make_phys<RS>(a);
   if (FAST) {
     ph.limiter = 1;  // van Leer
     ph.charlim = 1;

@@ -76,7 +76,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
   const bool cross = wtid < 320;
   if (tid < 2) tally.c[tid] = 0u;
   __syncthreads();
-  Phys<T> ph = make_phys(a);
+  Phys<T> ph = make_phys<RS>(a);
   if (FAST) {
     ph.limiter = 1;  // van Leer
     ph.charlim = 1;

@@ -66,7 +66,7 @@ __global__ void __launch_bounds__(threads<G>(), 2) vl_predict_kernel(FusedArgs<T
   // byte offset of the column's cell in a half-step plane (output columns)
   const unsigned wo = out_col ? (unsigned)(((y + Gs) * Ns + (x + Gs)) * (int)sizeof(T)) : 0u;
   int fails = 0, floors = 0;
-  Phys<T> ph = make_phys(a);
+  Phys<T> ph = make_phys<RS>(a);
 
   int seg = 0;
   // Work items: chunks of a group's output planes (a.zsplit per group, 1:

@@ -65,6 +65,7 @@ struct FusedArgs {
   long long n_groups;
   int g, nf;
   T gamma, theta, floor;
+  T gm1, inv_gm1;  // gamma - 1 and its inverse, rounded from double (the exact solver's)
   int limiter, charlim, roe_fb_hllc;
   unsigned long long* diag;
   // Single-segment launches pass their segment and time step by value

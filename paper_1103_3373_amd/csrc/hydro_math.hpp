@@ -606,9 +606,13 @@ HY_DEV V5<T> roe(const V5<T>& L, const V5<T>& R, const Phys<T>& ph, int* fails) 
   return F;
 }
 
-// Riemann dispatch: RS = 0 Roe, 1 HLLC, 2 HLLE.
+// The exact solver (riemann_exact.hpp, for the files that instantiate it).
+template <typename T> HY_DEV V5<T> exact_flux(const V5<T>& L, const V5<T>& R, const Phys<T>& ph, int* fails);
+
+// Riemann dispatch: RS = 0 Roe, 1 HLLC, 2 HLLE, 3 exact.
 template <int RS, typename T>
 HY_DEV V5<T> riemann(const V5<T>& L, const V5<T>& R, const Phys<T>& ph, int* fails) {
+  if constexpr (RS == 3) return exact_flux(L, R, ph, fails);
   if (RS == 1) return hllc(L, R, ph);
   if (RS == 2) return hlle(L, R, ph);
   return roe(L, R, ph, fails);

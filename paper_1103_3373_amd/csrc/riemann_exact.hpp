@@ -25,97 +25,104 @@ template <typename T> HY_DEV T xpow(T a, T b);
 template <> HY_DEV double xpow<double>(double a, double b) { return pow(a, b); }
 template <> HY_DEV float xpow<float>(float a, float b) { return powf(a, b); }
 
+// f_K(p) and its derivative.  On the rarefaction branch the derivative's power
+// p/p_K^-(gamma+1)/(2 gamma) is the one of f_K over p/p_K: one power a side.
 template <typename T>
-HY_DEV void exact_pfun(T p, T rk, T pk, T ck, const Phys<T>& ph, T& f, T& df) {
-  const T gp1 = ph.gamma + T(1);
+HY_DEV void exact_pfun(T p, T rk, T pk, T ck, T gm1, T gp1, T g1, T& f, T& df) {
   if (p > pk) {  // shock
     const T A = T(2) / (gp1 * rk);
-    const T B = ph.gm1 / gp1 * pk;
+    const T B = gm1 / gp1 * pk;
     const T q = sqrt(A / (p + B));
     f = (p - pk) * q;
     df = q * (T(1) - T(0.5) * (p - pk) / (B + p));
   } else {  // rarefaction
     const T pr = p / pk;
-    f = T(2) * ck / ph.gm1 * (xpow<T>(pr, ph.gm1 / (T(2) * ph.gamma)) - T(1));
-    df = T(1) / (rk * ck) * xpow<T>(pr, -gp1 / (T(2) * ph.gamma));
+    const T t = xpow<T>(pr, g1);
+    f = T(2) * ck / gm1 * (t - T(1));
+    df = t / (pr * rk * ck);
   }
 }
 
+// The sampled state's flux and 1 if the pair generates vacuum or the iteration
+// does not converge.  Not inlined: the Newton iteration dwarfs a call, and the
+// fused kernels solve at up to four places.
+template <typename T> struct ExactFlux {
+  V5<T> F;
+  int fail;
+};
 template <typename T>
-HY_DEV V5<T> exact_flux(const V5<T>& L, const V5<T>& R, const Phys<T>& ph, int* fails) {
-  const T gp1 = ph.gamma + T(1);
-  const T cL = sqrt(ph.gamma * L[4] / L[0]), cR = sqrt(ph.gamma * R[4] / R[0]);
+__device__ __attribute__((noinline)) ExactFlux<T> exact_solve(V5<T> L, V5<T> R, T gamma, T gm1, T inv_gm1) {
+  Phys<T> ph{};
+  ph.gamma = gamma;
+  ph.gm1 = gm1;
+  ph.inv_gm1 = inv_gm1;
+  const T gp1 = gamma + T(1), g1 = gm1 / (T(2) * gamma);
+  const T cL = sqrt(gamma * L[4] / L[0]), cR = sqrt(gamma * R[4] / R[0]);
   const T du = R[1] - L[1];
-  T p, u, rhoL, rhoR;
-  if (T(2) / ph.gm1 * (cL + cR) <= du) {  // vacuum is generated
-    ++*fails;
+  ExactFlux<T> r;
+  r.fail = 0;
+  T p, u;
+  const bool vacuum = T(2) / gm1 * (cL + cR) <= du;
+  if (vacuum) {
+    r.fail = 1;
     p = T(0);
     u = T(0.5) * (L[1] + R[1]);
-    rhoL = rhoR = T(0);
   } else {
     const T ppv = T(0.5) * (L[4] + R[4]) - T(0.125) * du * (L[0] + R[0]) * (cL + cR);
     p = fmax(ppv, T(1e-8) * fmin(L[4], R[4]));
     const T tol = sizeof(T) == 8 ? T(1e-15) : T(1e-6);
+    T fL, dL, fR, dR;
     int it = 0;
     for (; it < 200; ++it) {
-      T fL, dL, fR, dR;
-      exact_pfun(p, L[0], L[4], cL, ph, fL, dL);
-      exact_pfun(p, R[0], R[4], cR, ph, fR, dR);
+      exact_pfun(p, L[0], L[4], cL, gm1, gp1, g1, fL, dL);
+      exact_pfun(p, R[0], R[4], cR, gm1, gp1, g1, fR, dR);
       T pn = p - (fL + fR + du) / (dL + dR);
       if (pn < T(0)) pn = T(1e-12) * p;
       const T ch = T(2) * fabs(pn - p) / (pn + p);
       p = pn;
       if (ch < tol) break;
     }
-    if (it >= 200) ++*fails;
-    T fL, dL, fR, dR;
-    exact_pfun(p, L[0], L[4], cL, ph, fL, dL);
-    exact_pfun(p, R[0], R[4], cR, ph, fR, dR);
+    if (it >= 200) r.fail = 1;
+    exact_pfun(p, L[0], L[4], cL, gm1, gp1, g1, fL, dL);
+    exact_pfun(p, R[0], R[4], cR, gm1, gp1, g1, fR, dR);
     u = T(0.5) * (L[1] + R[1]) + T(0.5) * (fR - fL);
-    const T g6 = ph.gm1 / gp1;
-    rhoL = p > L[4] ? L[0] * (p / L[4] + g6) / (g6 * p / L[4] + T(1)) : L[0] * xpow<T>(p / L[4], T(1) / ph.gamma);
-    rhoR = p > R[4] ? R[0] * (p / R[4] + g6) / (g6 * p / R[4] + T(1)) : R[0] * xpow<T>(p / R[4], T(1) / ph.gamma);
   }
-  // Sample the solution on the face, x/t = 0.
-  V5<T> W;
-  if (T(0) <= u) {  // left of the contact
-    W = L;
-    if (p > L[4]) {  // left shock
-      const T SL = L[1] - cL * sqrt(gp1 / (T(2) * ph.gamma) * p / L[4] + ph.gm1 / (T(2) * ph.gamma));
-      if (!(T(0) <= SL)) { W[0] = rhoL; W[1] = u; W[4] = p; }
-    } else {  // left rarefaction
-      const T csL = cL * xpow<T>(p / L[4], ph.gm1 / (T(2) * ph.gamma));
-      const T head = L[1] - cL, tail = u - csL;
-      if (T(0) <= head) {
-      } else if (T(0) > tail) {
-        W[0] = rhoL; W[1] = u; W[4] = p;
-      } else {  // inside the fan
-        const T b = T(2) / gp1 + ph.gm1 / (gp1 * cL) * L[1];
-        W[0] = L[0] * xpow<T>(b, T(2) / ph.gm1);
-        W[1] = T(2) / gp1 * (cL + T(0.5) * ph.gm1 * L[1]);
-        W[4] = L[4] * xpow<T>(b, T(2) * ph.gamma / ph.gm1);
-      }
+  // Sample the solution on the face, x/t = 0: on the side K of the contact,
+  // with velocities counted away from the wave (mirrored for the right side),
+  // so that both sides are the left one.
+  const bool left = T(0) <= u;
+  const T sg = left ? T(1) : T(-1);
+  V5<T> W = left ? L : R;
+  const T c = left ? cL : cR, v = sg * W[1], us = sg * u, pk = W[4], pr = p / pk, g6 = gm1 / gp1;
+  if (p > pk) {  // shock
+    const T S = v - c * sqrt(gp1 / (T(2) * gamma) * p / pk + g1);
+    if (!(T(0) <= S)) {
+      W[0] = W[0] * (pr + g6) / (g6 * p / pk + T(1));
+      W[1] = u;
+      W[4] = p;
     }
-  } else {  // right of the contact
-    W = R;
-    if (p > R[4]) {  // right shock
-      const T SR = R[1] + cR * sqrt(gp1 / (T(2) * ph.gamma) * p / R[4] + ph.gm1 / (T(2) * ph.gamma));
-      if (!(T(0) >= SR)) { W[0] = rhoR; W[1] = u; W[4] = p; }
-    } else {  // right rarefaction
-      const T csR = cR * xpow<T>(p / R[4], ph.gm1 / (T(2) * ph.gamma));
-      const T head = R[1] + cR, tail = u + csR;
-      if (T(0) >= head) {
-      } else if (T(0) < tail) {
-        W[0] = rhoR; W[1] = u; W[4] = p;
-      } else {
-        const T b = T(2) / gp1 - ph.gm1 / (gp1 * cR) * R[1];
-        W[0] = R[0] * xpow<T>(b, T(2) / ph.gm1);
-        W[1] = T(2) / gp1 * (-cR + T(0.5) * ph.gm1 * R[1]);
-        W[4] = R[4] * xpow<T>(b, T(2) * ph.gamma / ph.gm1);
-      }
+  } else if (!(T(0) <= v - c)) {  // rarefaction with its head past the face
+    const T cs = c * xpow<T>(pr, g1);
+    if (T(0) > us - cs) {
+      W[0] = vacuum ? T(0) : W[0] * xpow<T>(pr, T(1) / gamma);
+      W[1] = u;
+      W[4] = p;
+    } else {  // inside the fan
+      const T b = T(2) / gp1 + gm1 / (gp1 * c) * v;
+      W[0] = W[0] * xpow<T>(b, T(2) / gm1);
+      W[1] = sg * (T(2) / gp1 * (c + T(0.5) * gm1 * v));
+      W[4] = pk * xpow<T>(b, T(2) * gamma / gm1);
     }
   }
-  return flux_of(W, ph);
+  r.F = flux_of(W, ph);
+  return r;
+}
+
+template <typename T>
+HY_DEV V5<T> exact_flux(const V5<T>& L, const V5<T>& R, const Phys<T>& ph, int* fails) {
+  const ExactFlux<T> r = exact_solve(L, R, ph.gamma, ph.gm1, ph.inv_gm1);
+  *fails += r.fail;
+  return r.F;
 }
 
 }  // namespace hy

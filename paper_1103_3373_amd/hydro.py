@@ -158,7 +158,7 @@ def ghost_width(scheme: int, recon: int) -> int:
 def solve_groups(inp, out, flux=None, *, dt, dh, gamma, scheme, recon, riemann, limiter=VANLEER, char=False,
                  plain=False, flux_mid=False, roe_fb_hllc=False, roe_fb_exact=False, stream=None):
     """One step of n patch groups: inp [n,5,N,N,N] -> out [n,5,16,16,16].
-    riemann=EXACT and roe_fb_exact run on the plain path."""
+    roe_fb_exact runs on the plain path."""
     n = inp.shape[0]
     N = 16 + 2 * ghost_width(scheme, recon)
     _require(inp, "inp", (n, 5, N, N, N))
