@@ -6,13 +6,19 @@
 //    is deterministic and equals a serial evaluation bit for bit), and FP64
 //    conserved sums with a fixed reduction order, in one launch; the time steps
 //    of a segment table in two.
-#include <limits.h>
 
 #include <type_traits>
 
 #include "hydro_internal.h"
 
 namespace hy {
+
+// Stores the q-th 16 bytes of an LDS array to the q-th of a 16-byte aligned
+// global one, around the caches (for outputs that are larger than they are).
+template <typename T> __device__ __forceinline__ void store16(T* dst, int q, const T* lds) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  __builtin_nontemporal_store(reinterpret_cast<const f4*>(lds)[q], reinterpret_cast<f4*>(dst) + q);
+}
 
 // ---------------------------------------------------------------------------
 // Periodic ghost fill.  Output groups [G][5][N][N][N], G = (gz*ngy+gy)*ngx+gx.
@@ -21,72 +27,108 @@ namespace hy {
 // ---------------------------------------------------------------------------
 // GC > 0: the ghost width fixed at compile time (no run-time integer
 // division per cell); GC == 0: g taken at run time.
-template <typename T, int GC>
+//
+// Bound by memory: 20 B written per ghosted FP32 cell and 20 B read, the reads
+// of ghost layers from L2.  Workgroups are dispatched to the 8 XCDs
+// round-robin, so XCD x takes the x-th eighth of the groups, whose neighbours
+// then share its L2 (the planes of one group used to spread over all of them).
+// WIDE (out 16-byte aligned; an N x N plane is a multiple of that): the planes
+// are passed through LDS and stored 16 bytes a lane, around the caches, which
+// the output would sweep of the input.  g = 3, FP32, plain box: 128^3 cells 49
+// -> 25 us, 192^3 198 -> 79 (148 through the caches), 256^3 480 -> 328 (396).
+// Below 64 groups (4 us) neither pays.
+template <typename T, int GC, bool WIDE>
 __global__ void __launch_bounds__(512) fill_periodic_kernel(const T* __restrict__ box, int nx, int ny, int nz, int g_rt,
-                                                            int grouped, T* __restrict__ out, long long g_off) {
-  // blockIdx.x = k in 0 .. N/2-1: the workgroup fills planes k and k + N/2
-  // of the padded group (N = 16 + 2g is even), all ten loads of a thread
-  // issued before its stores; blockIdx.y = group; threads cover the N x N
-  // plane, x fastest (coalesced writes).  Group counts stay below 2^31 (the
-  // caller checks), so the group coordinates use 32-bit division.
+                                                            int grouped, T* __restrict__ out, long long g_off, int cnt) {
+  // A workgroup fills planes k and k + 1 of a padded group (N = 16 + 2g is
+  // even; k even), all ten loads of a thread issued before its stores; threads
+  // cover the N x N plane, x fastest.  Group counts stay below 2^31 (the caller
+  // checks), so the group coordinates use 32-bit division.
+  __shared__ __align__(16) T sm[WIDE ? 10 * (16 + 2 * GC) * (16 + 2 * GC) : 1];
   const int g = GC > 0 ? GC : g_rt;
   const int N = 16 + 2 * g;
   const long long nc = (long long)N * N * N;
-  const int H = N / 2;
-  const int k = blockIdx.x;
-  const unsigned G = (unsigned)(g_off + blockIdx.y);
+  const unsigned H = N / 2, chunk = (cnt + 7) / 8;  // groups of an XCD
+  const bool by_xcd = gridDim.x != (unsigned)cnt * H;
+  const unsigned w = by_xcd ? blockIdx.x / 8 : blockIdx.x;
+  const unsigned gl = w / H + (by_xcd ? blockIdx.x % 8 * chunk : 0u);
+  const int k = 2 * (int)(w % H);
+  if (gl >= (unsigned)cnt) return;  // uniform
+  const unsigned G = (unsigned)(g_off + gl);
   const unsigned ngx = (unsigned)nx >> 4, ngy = (unsigned)ny >> 4;
   const long long boxc = (long long)nx * ny * nz;
   const int gx = (int)(G % ngx), gy = (int)((G / ngx) % ngy), gz = (int)(G / ngx / ngy);
-  int sz0 = gz * 16 + k - g, sz1 = sz0 + H;
+  int sz0 = gz * 16 + k - g, sz1 = sz0 + 1;
   sz0 += (sz0 < 0) ? nz : 0;
   sz0 -= (sz0 >= nz) ? nz : 0;
   sz1 += (sz1 < 0) ? nz : 0;
   sz1 -= (sz1 >= nz) ? nz : 0;
   T* o = out + (long long)G * 5 * nc + (long long)k * N * N;
-  const long long oH = (long long)H * N * N;
   for (int r = threadIdx.x; r < N * N; r += blockDim.x) {
     const int i = r % N, j = r / N;
     int sx = gx * 16 + i - g, sy = gy * 16 + j - g;
     sx += (sx < 0) ? nx : 0; sx -= (sx >= nx) ? nx : 0;
     sy += (sy < 0) ? ny : 0; sy -= (sy >= ny) ? ny : 0;
-    T v0[5], v1[5];
+    const T *s0, *s1;
+    long long vs;  // between variables
     if (grouped) {
       const long long base = ((long long)(sy >> 4) * ngx + (sx >> 4));
       const long long sg0 = (long long)(sz0 >> 4) * ngy * ngx + base, sg1 = (long long)(sz1 >> 4) * ngy * ngx + base;
       const int in = ((sy & 15) * 16 + (sx & 15));
-      const T* s0 = box + sg0 * 5 * 4096 + (sz0 & 15) * 256 + in;
-      const T* s1 = box + sg1 * 5 * 4096 + (sz1 & 15) * 256 + in;
-#pragma unroll
-      for (int n = 0; n < 5; ++n) { v0[n] = s0[n * 4096]; v1[n] = s1[n * 4096]; }
+      s0 = box + sg0 * 5 * 4096 + (sz0 & 15) * 256 + in;
+      s1 = box + sg1 * 5 * 4096 + (sz1 & 15) * 256 + in;
+      vs = 4096;
     } else {
-      const T* s0 = box + ((long long)sz0 * ny + sy) * nx + sx;
-      const T* s1 = box + ((long long)sz1 * ny + sy) * nx + sx;
-#pragma unroll
-      for (int n = 0; n < 5; ++n) { v0[n] = s0[n * boxc]; v1[n] = s1[n * boxc]; }
+      s0 = box + ((long long)sz0 * ny + sy) * nx + sx;
+      s1 = box + ((long long)sz1 * ny + sy) * nx + sx;
+      vs = boxc;
     }
+    T v0[5], v1[5];
+#pragma unroll
+    for (int n = 0; n < 5; ++n) { v0[n] = s0[n * vs]; v1[n] = s1[n * vs]; }
 #pragma unroll
     for (int n = 0; n < 5; ++n) {
-      o[n * nc + r] = v0[n];
-      o[n * nc + oH + r] = v1[n];
+      if constexpr (WIDE) {
+        sm[2 * n * N * N + r] = v0[n];
+        sm[(2 * n + 1) * N * N + r] = v1[n];
+      } else {
+        o[n * nc + r] = v0[n];
+        o[n * nc + N * N + r] = v1[n];
+      }
     }
   }
+  if constexpr (WIDE) {
+    __syncthreads();
+    const int Q = 2 * N * N * (int)sizeof(T) / 16;  // 16-byte pieces of two planes
+    for (int q = threadIdx.x; q < 5 * Q; q += blockDim.x) store16(o + (q / Q) * nc, q % Q, sm + (q / Q) * 2 * N * N);
+  }
+}
+
+template <typename T, int GC>
+static void go_fill_periodic(const T* box, int nx, int ny, int nz, int g, int grouped, T* out, long long g0, int cnt,
+                             hipStream_t st) {
+  const bool many = cnt >= 64;
+  const dim3 grid((unsigned)(many ? (cnt + 7) / 8 * 8 : cnt) * (unsigned)(8 + g));
+  if constexpr (GC > 0) {
+    if (many && (uintptr_t)out % 16 == 0) {
+      fill_periodic_kernel<T, GC, true><<<grid, dim3(512), 0, st>>>(box, nx, ny, nz, g, grouped, out, g0, cnt);
+      return;
+    }
+  }
+  fill_periodic_kernel<T, GC, false><<<grid, dim3(512), 0, st>>>(box, nx, ny, nz, g, grouped, out, g0, cnt);
 }
 
 template <typename T>
 hipError_t launch_fill_periodic(const T* box, int nx, int ny, int nz, int g, int grouped, T* out, hipStream_t st) {
-  const int N = 16 + 2 * g;
   const long long groups = (long long)(nx / 16) * (ny / 16) * (nz / 16);
-  if (groups == 0) return hipSuccess;
-  // grid.y is limited to 65535 groups per launch.
-  for (long long g0 = 0; g0 < groups; g0 += 65535) {
-    const long long cnt = groups - g0 < 65535 ? groups - g0 : 65535;
-    const dim3 grid(N / 2, (unsigned)cnt);
+  // at most 2^20 groups per launch: the grid stays below 2^31
+  for (long long g0 = 0; g0 < groups; g0 += 1 << 20) {
+    const int cnt = (int)(groups - g0 < (1 << 20) ? groups - g0 : (1 << 20));
     switch (g) {
-      case 2: fill_periodic_kernel<T, 2><<<grid, dim3(512), 0, st>>>(box, nx, ny, nz, g, grouped, out, g0); break;
-      case 3: fill_periodic_kernel<T, 3><<<grid, dim3(512), 0, st>>>(box, nx, ny, nz, g, grouped, out, g0); break;
-      case 4: fill_periodic_kernel<T, 4><<<grid, dim3(512), 0, st>>>(box, nx, ny, nz, g, grouped, out, g0); break;
-      default: fill_periodic_kernel<T, 0><<<grid, dim3(512), 0, st>>>(box, nx, ny, nz, g, grouped, out, g0); break;
+      case 2: go_fill_periodic<T, 2>(box, nx, ny, nz, g, grouped, out, g0, cnt, st); break;
+      case 3: go_fill_periodic<T, 3>(box, nx, ny, nz, g, grouped, out, g0, cnt, st); break;
+      case 4: go_fill_periodic<T, 4>(box, nx, ny, nz, g, grouped, out, g0, cnt, st); break;
+      default: go_fill_periodic<T, 0>(box, nx, ny, nz, g, grouped, out, g0, cnt, st); break;
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -274,11 +316,24 @@ hipError_t launch_group_map(const int* layout, int n_groups, int ng0, int n_leve
 // moves.  When the coarse points that the group's padded region touches fit
 // in kFoot^3 (levels at least about 4x finer than the coarse field), the
 // workgroup first blends them once into LDS and the columns interpolate
-// from there; otherwise every column blends from global memory.  Both give
-// the same values.  No contraction: a plain FP64 evaluation of that
+// from there; when one layer of them fits in kSide^2 (levels as fine as the
+// coarse field), it blends a layer at a time; otherwise every column blends
+// from global memory.  All give the same values.  No contraction: a plain FP64 evaluation of that
 // expression.  Map entries outside [0, n_groups) count as empty, and levels
 // are clamped into range, so every access stays inside the arrays whatever
 // the layout holds.
+//
+// The floor is memory (FP32, g = 3: 213 KB written and 82 KB read a group,
+// 1.16 ms for 20,480 groups at 5.2 TB/s).  It took 2.0 ms, bound by its
+// instructions (every cell formed its plane's coarse coordinate in FP64 and
+// tested three sources) and by stores of 4 bytes a lane.  A column meets three
+// z ranges (below the group, its own planes, above), each a copy from one
+// group or an interpolation throughout, so the sources are chosen once per
+// range, and the planes' coarse layers and weights come from a table: 1.56 ms.
+// Two planes at a time then pass through LDS and are stored 16 bytes a lane
+// around the caches: 1.36 ms.  (Such stores of 4 bytes a lane were slower, 1.9
+// ms: they split the 128-byte lines of a 22 x 22 plane.)  Small launches split
+// a group's planes over gridDim.y workgroups.
 template <typename T>
 struct AmrArgs {
   const T* fine;       // [n][5][16][16][16]
@@ -291,14 +346,22 @@ struct AmrArgs {
   double alpha[8];
 };
 
-constexpr int kFoot = 8;  // coarse points per axis staged in LDS
+constexpr int kFoot = 8;   // coarse points per axis staged in LDS as a whole
+constexpr int kSide = 25;  // coarse points per axis of a layer staged in LDS
+static_assert(kSide * kSide >= kFoot * kFoot * kFoot, "one buffer serves both");
 
 template <typename T, int G>
 __global__ void __launch_bounds__(interp_threads<G>()) fill_amr_group_kernel(AmrArgs<T> a) {
 #pragma clang fp contract(off)
   constexpr int N = 16 + 2 * G;
   constexpr long long nc = (long long)N * N * N;
-  __shared__ double sB[5][kFoot * kFoot * kFoot];  // blended coarse footprint, [n][z][y][x]
+  __shared__ double sB[5][kSide * kSide];  // blended coarse points: the footprint [z][y][x] or a layer [y][x]
+  __shared__ double sAz[N];                // z weight of each plane
+  __shared__ int sZ[N];                    // its lower coarse layer (unwrapped)
+  __shared__ __align__(16) T sm[10 * N * N];  // two finished planes of the five variables
+  // The workgroup's planes, an even number.
+  const int kb = 2 * ((int)blockIdx.y * (N / 2) / (int)gridDim.y);
+  const int ke = 2 * (((int)blockIdx.y + 1) * (N / 2) / (int)gridDim.y);
   const int cn = a.cn;
   const long long cc = (long long)cn * cn * cn;
   const long long grp = blockIdx.x;
@@ -318,43 +381,56 @@ __global__ void __launch_bounds__(interp_threads<G>()) fill_amr_group_kernel(Amr
   // along an axis whose group origin is o.
   auto coord = [&](int o, int c) -> double { return (((double)o + c) + 0.5) * dh * cn - 0.5; };
   // Footprint: unwrapped coarse indices lo .. lo + W - 1 per axis.
-  const int lox = (int)floor(coord(L.y, -G)), loy = (int)floor(coord(L.z, -G)), loz = (int)floor(coord(L.w, -G));
+  const int lox = (int)floor(coord(L.y, -G)), loy = (int)floor(coord(L.z, -G)), loz = (int)floor(coord(L.w, kb - G));
   const int wx = (int)floor(coord(L.y, 15 + G)) + 2 - lox, wy = (int)floor(coord(L.z, 15 + G)) + 2 - loy,
-            wz = (int)floor(coord(L.w, 15 + G)) + 2 - loz;
+            wz = (int)floor(coord(L.w, ke - 1 - G)) + 2 - loz;
   // Uniform over the workgroup.  Origins outside the level take the direct
   // path, whose indices all wrap.
-  const bool staged = L.y >= 0 && L.y < nl && L.z >= 0 && L.z < nl && L.w >= 0 && L.w < nl && wx <= kFoot &&
-                      wy <= kFoot && wz <= kFoot;
+  const bool inside = L.y >= 0 && L.y < nl && L.z >= 0 && L.z < nl && L.w >= 0 && L.w < nl;
+  const bool staged = inside && wx <= kFoot && wy <= kFoot && wz <= kFoot;
+  const bool layered = inside && !staged && wx <= kSide && wy <= kSide;
+  // Blended coarse values of point (ix, iy) of the footprint in layer zu.
+  auto blend = [&](int ix, int iy, int zu, int p) {
+    const long long g = ((long long)wrap_index((long long)zu, cn) * cn + wrap_index((long long)loy + iy, cn)) * cn +
+                        wrap_index((long long)lox + ix, cn);
+    T u0[5], u1[5];
+#pragma unroll
+    for (int n = 0; n < 5; ++n) { u0[n] = a.c0[n * cc + g]; u1[n] = a.c1[n * cc + g]; }
+#pragma unroll
+    for (int n = 0; n < 5; ++n) sB[n][p] = (1.0 - al) * (double)u0[n] + al * (double)u1[n];
+  };
   if (staged) {
-    for (int q = r; q < 5 * kFoot * kFoot * kFoot; q += blockDim.x) {
-      const int n = q / (kFoot * kFoot * kFoot), p = q % (kFoot * kFoot * kFoot);
+    for (int p = r; p < kFoot * kFoot * kFoot; p += blockDim.x) {
       const int ix = p % kFoot, iy = (p / kFoot) % kFoot, iz = p / (kFoot * kFoot);
-      if (ix < wx && iy < wy && iz < wz) {
-        const long long g = (long long)n * cc +
-                            ((long long)wrap_index((long long)loz + iz, cn) * cn + wrap_index((long long)loy + iy, cn)) *
-                                cn +
-                            wrap_index((long long)lox + ix, cn);
-        sB[n][p] = (1.0 - al) * (double)a.c0[g] + al * (double)a.c1[g];
-      }
+      if (ix < wx && iy < wy && iz < wz) blend(ix, iy, loz + iz, p);
     }
-    __syncthreads();
   }
-  if (r >= N * N) return;  // no barrier below
-  const int ci = r % N - G, cj = r / N - G;
+  if (r < N) {
+    const double Z = coord(L.w, r - G), fz0 = floor(Z);
+    sAz[r] = Z - fz0;
+    sZ[r] = (int)fz0;
+  }
+  __syncthreads();
+  const bool column = r < N * N;  // the others help at the barriers
+  const int rc = column ? r : 0;
+  const int ci = rc % N - G, cj = rc / N - G;
   const bool in_xy = ci >= 0 && ci < 16 && cj >= 0 && cj < 16;
   const int px = wrap_index((long long)L.y + ci, nl), py = wrap_index((long long)L.z + cj, nl);
+  const int pz0 = wrap_index((long long)L.w, nl) & 15;  // 0 for origins on the 16-cell grid
   const double X = coord(L.y, ci), Y = coord(L.z, cj);
   const double fx0 = floor(X), fy0 = floor(Y);
   const double ax = X - fx0, ay = Y - fy0;
   const int x0 = wrap_index((long long)fx0, cn), y0 = wrap_index((long long)fy0, cn);
   const int x1 = x0 + 1 == cn ? 0 : x0 + 1, y1 = y0 + 1 == cn ? 0 : y0 + 1;
   const int sx = (int)fx0 - lox, sy = (int)fy0 - loy;  // staged footprint indices
-  // x-y interpolation of layer z (unwrapped coarse index) of variable n.
+  // x-y interpolation of layer z (unwrapped coarse index) of variable n; with
+  // layered, of the layer that sB holds.
   auto layer = [&](int zu, int n) -> double {
-    if (staged) {
-      const double* f = sB[n] + (zu - loz) * kFoot * kFoot;
-      const double v00 = (1.0 - ax) * f[sy * kFoot + sx] + ax * f[sy * kFoot + sx + 1];
-      const double v01 = (1.0 - ax) * f[(sy + 1) * kFoot + sx] + ax * f[(sy + 1) * kFoot + sx + 1];
+    if (staged || layered) {
+      const int w = staged ? kFoot : kSide;
+      const double* f = sB[n] + (staged ? (zu - loz) * kFoot * kFoot : 0) + sy * w + sx;
+      const double v00 = (1.0 - ax) * f[0] + ax * f[1];
+      const double v01 = (1.0 - ax) * f[w] + ax * f[w + 1];
       return (1.0 - ay) * v00 + ay * v01;
     }
     const long long base = (long long)n * cc + (long long)wrap_index(zu, cn) * cn * cn;
@@ -365,63 +441,115 @@ __global__ void __launch_bounds__(interp_threads<G>()) fill_amr_group_kernel(Amr
     const double v01 = (1.0 - ax) * b(y1 * cn + x0) + ax * b(y1 * cn + x1);
     return (1.0 - ay) * v00 + ay * v01;
   };
-  const T* own = a.fine + grp * 5 * 4096;
-  T* o = a.out + grp * 5 * nc + r;
   // The column meets three group positions along z (below, its own, above;
-  // G < 16): their map entries are read once, before the march.
-  int owner3[3];
+  // G < 16): the cells it copies there (null: it interpolates).
+  const T* src[3];
   {
     const long long gzc = wrap_index((long long)L.w, nl) >> 4;
+    const int in = (py & 15) * 16 + (px & 15);
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
       long long gz = gzc + t - 1;
       gz += gz < 0 ? ng : 0;
       gz -= gz >= ng ? ng : 0;
       const int ow = a.map[moff + (gz * ng + (py >> 4)) * ng + (px >> 4)];
-      owner3[t] = (ow >= 0 && ow < a.n_groups) ? ow : -1;
+      src[t] = ow >= 0 && ow < a.n_groups ? a.fine + (long long)ow * 5 * 4096 + in : nullptr;
     }
+    if (in_xy) src[1] = a.fine + grp * 5 * 4096 + cj * 16 + ci;
   }
   double v0[5], v1[5];
-  long long zc = LLONG_MIN;  // unwrapped coarse layer of v0 (none yet)
-  for (int k = 0; k < N; ++k) {
-    const int ck = k - G;
-    T val[5];
-    if (in_xy && ck >= 0 && ck < 16) {
+  bool have = false;
+  int zc = 0;  // unwrapped coarse layer of v0 (if any), the same for all columns of the wavefront
+  // A layer at a time, by all threads (the caller is uniform).
+  auto load_layer = [&](int zu, double (&v)[5]) {
+    __syncthreads();  // the previous layer has been read
+    for (int p = r; p < wx * wy; p += blockDim.x) blend(p % wx, p / wx, zu, p / wx * kSide + p % wx);
+    __syncthreads();
 #pragma unroll
-      for (int n = 0; n < 5; ++n) val[n] = own[n * 4096 + (ck * 16 + cj) * 16 + ci];
-    } else {
-      const int pz = wrap_index((long long)L.w + ck, nl);
-      const int owner = owner3[ck < 0 ? 0 : (ck < 16 ? 1 : 2)];
-      if (owner >= 0) {
-        const T* s = a.fine + (long long)owner * 5 * 4096 + ((pz & 15) * 16 + (py & 15)) * 16 + (px & 15);
+    for (int n = 0; n < 5; ++n) v[n] = layer(zu, n);
+  };
+  // Where plane k of the column comes from.
+  auto source = [&](int k) -> const T* {
+    const int t = k < G ? 0 : (k < G + 16 ? 1 : 2);
+    const T* s = src[t];
+    return s ? s + (((t == 1 && in_xy ? 0 : pz0) + k - G) & 15) * 256 : nullptr;
+  };
+  // The copied cells of two planes are requested while the two before them are
+  // stored.
+  T next[2][5];
+  auto request = [&](int k) {
 #pragma unroll
-        for (int n = 0; n < 5; ++n) val[n] = s[n * 4096];
-      } else {
-        const double Z = coord(L.w, ck);
-        const double fz0 = floor(Z);
-        const double az = Z - fz0;
-        const long long z0 = (long long)fz0;
-        if (z0 != zc) {
-          const bool shift = z0 == zc + 1;
+    for (int p = 0; p < 2; ++p) {
+      const T* q = source(k + p);
+      if (q) {
 #pragma unroll
-          for (int n = 0; n < 5; ++n) {
-            v0[n] = shift ? v1[n] : layer((int)z0, n);
-            v1[n] = layer((int)z0 + 1, n);
-          }
-          zc = z0;
-        }
-#pragma unroll
-        for (int n = 0; n < 5; ++n) val[n] = (T)((1.0 - az) * v0[n] + az * v1[n]);
+        for (int n = 0; n < 5; ++n) next[p][n] = q[n * 4096];
       }
     }
+  };
+  T* og = a.out + grp * 5 * nc;
+  const bool wide = (uintptr_t)a.out % 16 == 0;  // uniform
+  request(kb);
+  for (int k = kb; k < ke; k += 2) {
 #pragma unroll
-    for (int n = 0; n < 5; ++n) o[n * nc + (long long)k * N * N] = val[n];
+    for (int p = 0; p < 2; ++p) {
+      const bool copied = source(k + p) != nullptr;
+      T val[5];
+#pragma unroll
+      for (int n = 0; n < 5; ++n) val[n] = next[p][n];
+      if (layered || __any(!copied)) {
+        const int z = __builtin_amdgcn_readfirstlane(sZ[k + p]);
+        const double az = sAz[k + p], bz = 1.0 - az;
+        if (!have || z != zc) {
+          const bool shift = have && z == zc + 1;
+          if (layered) {
+            if (shift) {
+#pragma unroll
+              for (int n = 0; n < 5; ++n) v0[n] = v1[n];
+            } else {
+              load_layer(z, v0);
+            }
+            load_layer(z + 1, v1);
+          } else {
+#pragma unroll
+            for (int n = 0; n < 5; ++n) {
+              v0[n] = shift ? v1[n] : layer(z, n);
+              v1[n] = layer(z + 1, n);
+            }
+          }
+          zc = z;
+          have = true;
+        }
+        if (!copied) {
+#pragma unroll
+          for (int n = 0; n < 5; ++n) val[n] = (T)(bz * v0[n] + az * v1[n]);
+        }
+      }
+      if (column) {
+#pragma unroll
+        for (int n = 0; n < 5; ++n) sm[(2 * n + p) * N * N + r] = val[n];
+      }
+    }
+    if (k + 2 < ke) request(k + 2);
+    __syncthreads();
+    constexpr int C = 2 * N * N, Q = C * (int)sizeof(T) / 16;
+    T* o = og + (long long)k * N * N;
+    if (wide) {
+      for (int q = r; q < 5 * Q; q += blockDim.x) store16(o + (q / Q) * nc, q % Q, sm + (q / Q) * C);
+    } else {
+      for (int q = r; q < 5 * C; q += blockDim.x) o[(q / C) * nc + q % C] = sm[q];
+    }
+    __syncthreads();
   }
 }
 
 template <typename T, int G>
 static hipError_t launch_amr_g(const AmrArgs<T>& a, hipStream_t st) {
-  fill_amr_group_kernel<T, G><<<dim3((unsigned)a.n_groups), dim3(interp_threads<G>()), 0, st>>>(a);
+  // Workgroups per group: 60 groups (FP32, g = 3) 23.5 us with one, 11.5 with
+  // four; 600 groups 45.8 / 43.7 / 49.6 us with 1 / 2 / 4; 2,600 groups 178 /
+  // 193 with 1 / 2 (each stages its coarse points anew).
+  const int ns = a.n_groups <= 128 ? 4 : (a.n_groups <= 1000 ? 2 : 1);
+  fill_amr_group_kernel<T, G><<<dim3((unsigned)a.n_groups, (unsigned)ns), dim3(interp_threads<G>()), 0, st>>>(a);
   return hipGetLastError();
 }
 
