@@ -352,7 +352,7 @@ int hydro_autotune(const struct hydro_spec* spec, int n_groups_hint, void* strea
  * larger than a launch's work-item count is clamped to it).  variant =
  * register budget variant: 2 (one workgroup per CU, no register spills) or 4
  * (two workgroups per CU; FP32 only).  zrun = tile depth of a box step
- * without flux output (hydro_step_box; for VL, of its second stage): each
+ * (hydro_step_box; for VL, of its second stage): each
  * workgroup marches through zrun z-consecutive patch groups of one column in
  * one pass (a 16 x 16 x 16*zrun tile), so the work items are the box's
  * groups / zrun; 0 = default (the largest of 4, 2 that divides the box's
@@ -375,8 +375,8 @@ int hydro_set_launch_shape(const struct hydro_spec* spec, int grid, int variant,
 
 /*
  * The launch shape hydro_step_box would use for `spec` on an nx x ny x nz
- * box without flux output (host outputs: workgroups, register variant, and
- * groups per z-run).  No device work.
+ * box, with flux output or without (host outputs: workgroups, register
+ * variant, and groups per z-run).  No device work.
  * HYDRO_EINVAL for bad sizes or options.
  */
 int hydro_get_launch_shape(const struct hydro_spec* spec, int nx, int ny, int nz, int* grid, int* variant,

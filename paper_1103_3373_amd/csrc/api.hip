@@ -290,7 +290,7 @@ Tune split_small(Tune t, int f64, int scheme, long long n_groups, bool shared = 
 }
 
 // Launch shape of a step over one periodic box of ngz groups in z
-// (n_groups in all) without flux output: the z-run length (the tuned one,
+// (n_groups in all): the z-run length (the tuned one,
 // or the largest of 4, 2 that divides ngz and still leaves two runs per
 // resident workgroup slot; in any case the largest built length, not above
 // it, that divides ngz) and the grid over the runs.
@@ -519,11 +519,9 @@ int hydro_step_box(const void* box_in, void* box_out, void* flux_out, int nx, in
   if (int rc = device_state(&ds)) return rc;
   hy::Seg seg{box_in, box_out, flux_out, dt_dev, dt_scale, dh, 0, G, nx / 16, ny / 16, nz / 16, 1};
   const int g = ghost_width(scheme, reconstruction);
-  // Without flux output the workgroups march through runs of z-consecutive
-  // groups.
-  const Tune tu = !flux_out ? tuned_box(f64, scheme, reconstruction, riemann, limiter, charlim, G, nz / 16)
-                            : split_small(tuned(f64, scheme, reconstruction, riemann, charlim, G), f64, scheme, G);
-  const int zrun = !flux_out ? tu.zrun : 1;
+  // The workgroups march through runs of z-consecutive groups.
+  const Tune tu = tuned_box(f64, scheme, reconstruction, riemann, limiter, charlim, G, nz / 16);
+  const int zrun = tu.zrun;
   Workspace& w = ds->ws[st];
   if (int rc = ensure_vl(w, (size_t)G * hy::fused_scratch_per_group(scheme, reconstruction, 1) * esz)) return rc;
   // Passed by value: the kernel reads dt through seg.dt (segs == nullptr and

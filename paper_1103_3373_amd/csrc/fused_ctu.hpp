@@ -101,6 +101,15 @@ template <typename T> HY_DEV V5<T> other_frame_d(const V5<T>& v, bool d) {
   return r;
 }
 
+// A per-lane value that the compiler takes as new here: what a run's flux
+// stores form from it is not carried in registers through the plane loop
+// (256^3 with flux in runs of 4: HLLC 1244 -> 1223 us, Roe 1676 -> 1655; MHM,
+// with registers to spare, and single groups gain nothing).
+HY_DEV int here(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // WAVES = minimum waves per SIMD the register allocation must allow: 2 gives
 // one workgroup per CU without spills, 4 gives two workgroups per CU (with
 // some spilling); the autotuner picks per specialization.
@@ -111,10 +120,16 @@ template <typename T> HY_DEV V5<T> other_frame_d(const V5<T>& v, bool d) {
 // every other combination runs the same code with run-time choices.
 //
 // ZR: groups per work item (tile depth 16 * ZR): ZR > 1 only for a single
-// periodic box without flux output (a.zrun == ZR).  ZR = 0: a work item is a
-// chunk of a group, 1/a.zsplit of its planes, for launches with too few
-// groups to fill the chip.
-template <typename T, bool PPM, int RS, int WAVES, bool FAST, int ZR>
+// periodic box (a.zrun == ZR).  ZR = 0: a work item is a chunk of a group,
+// 1/a.zsplit of its planes, for launches with too few groups to fill the chip.
+//
+// FLUX: the launch may store face fluxes (always so for a segment table, whose
+// pointers the host does not see).  Without them the kernel keeps fewer scalar
+// registers live and spills less: 128^3 CTU 170 -> 162 us, MHM 122 -> 117,
+// 192 x 160 x 144 CTU 407 -> 377, with the same bits.  A box step with fluxes
+// takes runs as well: 256^3 Roe 1708 -> 1655 us, HLLC 1278 -> 1223, MHM
+// 907 -> 871, against one group per run.
+template <typename T, bool PPM, int RS, int WAVES, bool FAST, int ZR, bool FLUX>
 __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T> a) {
   constexpr int NT = kThreads;
   constexpr int G = PPM ? 3 : 2;
@@ -158,7 +173,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
   constexpr int nS = wS * 18;
 
   // Work items: single groups, or runs of ZR z-consecutive groups of one
-  // periodic box (flux output off), marched through in one pass: the z
+  // periodic box, marched through in one pass: the z
   // prologue and the two planes beyond each end are paid once per run.
   constexpr bool SPLIT = ZR == 0;
   constexpr int KR = SPLIT ? 1 : ZR;
@@ -183,7 +198,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
       gzs = nxy;
     }
     T* __restrict__ O = reinterpret_cast<T*>(S.out) + lg * 5 * 4096;
-    T* __restrict__ FO = (ZR <= 1 && S.flux) ? reinterpret_cast<T*>(S.flux) + lg * 3 * a.nf * 5 * 256 : nullptr;
+    T* __restrict__ FO = (FLUX && S.flux) ? reinterpret_cast<T*>(S.flux) + lg * 3 * a.nf * 5 * 256 : nullptr;
     // A box segment beyond the addressing limit gets NaN outputs: a NaN dt/dh
     // makes every updated cell NaN, and the face fluxes get NaN added.
     const T poison = slab_fits<T>(S) ? T(0) : T(__builtin_nan(""));
@@ -462,22 +477,45 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
         }
         if (FO) {
           // z face z0 + t of the group (a chunk's last face is the next one's first)
-          const int p = z0 + t;
-          const int f = (p == 0) ? 0 : (p == 16 ? 1 : (p == 8 && a.nf == 3 ? 2 : -1));
-          if (f >= 0 && (t >= 0 && (t < nzt || p == 16))) {
+          const int p = z0 + t, yx = ZR > 1 ? here(tid) : tid;  // tid = y 16 + x
+          if constexpr (ZR <= 1) {
+            const int f = (p == 0) ? 0 : (p == 16 ? 1 : (p == 8 && a.nf == 3 ? 2 : -1));
+            if (f >= 0 && (t >= 0 && (t < nzt || p == 16))) {
 #pragma unroll
-            for (int n = 0; n < 5; ++n) gstore(FO + ((2 * a.nf + f) * 5 + n) * 256, (unsigned)(y * 16 + x) * (unsigned)sizeof(T), hn[n] + poison);
+              for (int n = 0; n < 5; ++n) gstore(FO + ((2 * a.nf + f) * 5 + n) * 256, (unsigned)yx * (unsigned)sizeof(T), hn[n] + poison);
+            }
+          } else {
+            // A run: the lower or mid face of plane t's group, and the upper
+            // face of the group below.
+            const long gstride = (long)gzs * (3 * a.nf * 5 * 256);
+            const int f = (t & 15) == 0 ? 0 : ((t & 15) == 8 && a.nf == 3 ? 2 : -1);
+            if (t >= 0 && t < nzt && f >= 0) {
+              T* Fg = FO + (t >> 4) * gstride + (2 * a.nf + f) * 5 * 256;
+#pragma unroll
+              for (int n = 0; n < 5; ++n) gstore(Fg + n * 256, (unsigned)yx * (unsigned)sizeof(T), hn[n] + poison);
+            }
+            if (t > 0 && f == 0) {
+              T* Fg = FO + ((t >> 4) - 1) * gstride + (2 * a.nf + 1) * 5 * 256;
+#pragma unroll
+              for (int n = 0; n < 5; ++n) gstore(Fg + n * 256, (unsigned)yx * (unsigned)sizeof(T), hn[n] + poison);
+            }
           }
         }
       } else if (FO && t >= 0 && t < nzt) {
-        const int q = tid - 256;
+        const int q = (ZR > 1 ? here(tid) : tid) - 256;
         if (q < 2 * a.nf * 16) {
           const bool d = q >= a.nf * 16;
           const int f = (q / 16) % a.nf, s = q % 16;
+          T* Fg = FO;
+          int zg = z0 + t;  // plane in its group
+          if constexpr (ZR > 1) {
+            Fg += (long)(t >> 4) * gzs * (3 * a.nf * 5 * 256);
+            zg = t & 15;
+          }
           const int fi = f == 0 ? -1 : (f == 1 ? 15 : 7);  // face index of offsets 0, 16, 8
           const V5<T> v = from_frame_d(lds5(sF2 + (d ? 5 * kF2 : 0), kF2, s * 17 + fi + 1), d);
 #pragma unroll
-          for (int n = 0; n < 5; ++n) gstore(FO + (((d ? 1 : 0) * a.nf + f) * 5 + n) * 256, (unsigned)((z0 + t) * 16 + s) * (unsigned)sizeof(T), v[n] + poison);
+          for (int n = 0; n < 5; ++n) gstore(Fg + (((d ? 1 : 0) * a.nf + f) * 5 + n) * 256, (unsigned)(zg * 16 + s) * (unsigned)sizeof(T), v[n] + poison);
         }
       }
       if (cross) {

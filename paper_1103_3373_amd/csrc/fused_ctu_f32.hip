@@ -7,9 +7,9 @@ namespace hy {
 
 hipError_t launch_ctu_f32_roe(const FusedArgs<float>& a, int recon, int waves, bool fast, int grid, hipStream_t st);
 
-template <bool PPM, int RS, int WAVES, bool FAST, int ZR>
+template <bool PPM, int RS, int WAVES, bool FAST, int ZR, bool FLUX>
 static hipError_t launch_zr(const FusedArgs<float>& a, int grid, hipStream_t st) {
-  auto k = ctu::ctu_fused_kernel<float, PPM, RS, WAVES, FAST, ZR>;
+  auto k = ctu::ctu_fused_kernel<float, PPM, RS, WAVES, FAST, ZR, FLUX>;
   const size_t shm = ctu::kLdsBytes(sizeof(float));
   static std::atomic<unsigned long long> lds_set{0};
   const hipError_t e = raise_lds_limit((const void*)k, shm, lds_set);
@@ -20,16 +20,23 @@ static hipError_t launch_zr(const FusedArgs<float>& a, int grid, hipStream_t st)
 
 template <bool PPM, int RS, int WAVES, bool FAST>
 static hipError_t launch_one(const FusedArgs<float>& a, int grid, hipStream_t st) {
+  const bool flux = has_flux(a);
   if (a.zsplit > 1) {
-    if constexpr (WAVES == 4) return launch_zr<PPM, RS, WAVES, FAST, 0>(a, grid, st);
+    if constexpr (WAVES == 4)
+      return flux ? launch_zr<PPM, RS, WAVES, FAST, 0, true>(a, grid, st) : launch_zr<PPM, RS, WAVES, FAST, 0, false>(a, grid, st);
     return hipErrorInvalidValue;
   }
   if constexpr (WAVES == 4 && FAST) {
-    if (a.zrun == 2) return launch_zr<PPM, RS, WAVES, FAST, 2>(a, grid, st);
-    if (a.zrun == 4) return launch_zr<PPM, RS, WAVES, FAST, 4>(a, grid, st);
+    if (a.zrun == 2)
+      return flux ? launch_zr<PPM, RS, WAVES, FAST, 2, true>(a, grid, st) : launch_zr<PPM, RS, WAVES, FAST, 2, false>(a, grid, st);
+    if (a.zrun == 4)
+      return flux ? launch_zr<PPM, RS, WAVES, FAST, 4, true>(a, grid, st) : launch_zr<PPM, RS, WAVES, FAST, 4, false>(a, grid, st);
   }
   if (a.zrun != 1) return hipErrorInvalidValue;
-  return launch_zr<PPM, RS, WAVES, FAST, 1>(a, grid, st);
+  if constexpr (WAVES == 4) {
+    if (!flux) return launch_zr<PPM, RS, WAVES, FAST, 1, false>(a, grid, st);
+  }
+  return launch_zr<PPM, RS, WAVES, FAST, 1, true>(a, grid, st);
 }
 
 template <int WAVES, bool FAST>

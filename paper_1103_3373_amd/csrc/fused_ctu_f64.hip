@@ -3,9 +3,9 @@
 
 namespace hy {
 
-template <bool PPM, int RS, int WAVES, bool FAST, int ZR>
+template <bool PPM, int RS, int WAVES, bool FAST, int ZR, bool FLUX>
 static hipError_t launch_zr(const FusedArgs<double>& a, int grid, hipStream_t st) {
-  auto k = ctu::ctu_fused_kernel<double, PPM, RS, WAVES, FAST, ZR>;
+  auto k = ctu::ctu_fused_kernel<double, PPM, RS, WAVES, FAST, ZR, FLUX>;
   const size_t shm = ctu::kLdsBytes(sizeof(double));
   static std::atomic<unsigned long long> lds_set{0};
   const hipError_t e = raise_lds_limit((const void*)k, shm, lds_set);
@@ -17,8 +17,12 @@ static hipError_t launch_zr(const FusedArgs<double>& a, int grid, hipStream_t st
 template <bool PPM, int RS, int WAVES, bool FAST>
 static hipError_t launch_one(const FusedArgs<double>& a, int grid, hipStream_t st) {
   if (a.zrun != 1) return hipErrorInvalidValue;  // one group (or a part of one) per work item in FP64
-  if (a.zsplit > 1) return launch_zr<PPM, RS, WAVES, FAST, 0>(a, grid, st);
-  return launch_zr<PPM, RS, WAVES, FAST, 1>(a, grid, st);
+  const bool flux = has_flux(a);
+  if (a.zsplit > 1)
+    return flux ? launch_zr<PPM, RS, WAVES, FAST, 0, true>(a, grid, st)
+                : launch_zr<PPM, RS, WAVES, FAST, 0, false>(a, grid, st);
+  return flux ? launch_zr<PPM, RS, WAVES, FAST, 1, true>(a, grid, st)
+              : launch_zr<PPM, RS, WAVES, FAST, 1, false>(a, grid, st);
 }
 
 template <int WAVES, bool FAST>

@@ -27,10 +27,10 @@ hipError_t solve(const FusedArgs<T>& a, int grid, hipStream_t st) {
   constexpr int W = sizeof(T) == 8 ? 2 : 4;
   static std::atomic<unsigned long long> lds_set{0};
   if constexpr (SCHEME == 2)
-    return go<T>(ctu::ctu_fused_kernel<T, PPM, 3, W, false, ZR>, fz::kThreads, ctu::kLdsBytes(sizeof(T)), lds_set, a,
+    return go<T>(ctu::ctu_fused_kernel<T, PPM, 3, W, false, ZR, true>, fz::kThreads, ctu::kLdsBytes(sizeof(T)), lds_set, a,
                  grid, st);
   else
-    return go<T>(muscl::muscl_kernel<T, PPM, 3, W, SCHEME, false, ZR>, fz::kThreads, muscl::kLdsBytes(sizeof(T)),
+    return go<T>(muscl::muscl_kernel<T, PPM, 3, W, SCHEME, false, ZR, true>, fz::kThreads, muscl::kLdsBytes(sizeof(T)),
                  lds_set, a, grid, st);
 }
 

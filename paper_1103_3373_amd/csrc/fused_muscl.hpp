@@ -47,9 +47,9 @@ constexpr size_t kLdsBytes(size_t elem) { return kLds * elem + 2 * sizeof(unsign
 
 // FAST as in the CTU kernel: van Leer on characteristic variables fixed at
 // compile time.  ZR as in the CTU kernel: groups per work item (tile depth
-// 16 * ZR), ZR > 1 only for a single periodic box without flux output; ZR = 0
-// a chunk of a group (a.zsplit).
-template <typename T, bool PPM, int RS, int WAVES, int MODE, bool FAST, int ZR>
+// 16 * ZR), ZR > 1 only for a single periodic box; ZR = 0 a chunk of a
+// group (a.zsplit).  FLUX as in the CTU kernel.
+template <typename T, bool PPM, int RS, int WAVES, int MODE, bool FAST, int ZR, bool FLUX>
 __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) {
   constexpr int NT = kThreads;
   constexpr int G = PPM ? 3 : 2;
@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
     }
     const long long grp = S.first + lg;
     T* __restrict__ O = reinterpret_cast<T*>(S.out) + lg * 5 * 4096;
-    T* __restrict__ FO = (ZR <= 1 && S.flux) ? reinterpret_cast<T*>(S.flux) + lg * 3 * a.nf * 5 * 256 : nullptr;
+    T* __restrict__ FO = (FLUX && S.flux) ? reinterpret_cast<T*>(S.flux) + lg * 3 * a.nf * 5 * 256 : nullptr;
     ph.dtdh = (T)(dt / S.dh);
     ph.hdtdh = (T)(0.5 * dt / S.dh);
     // A segment that is no box in a launch that declared boxes only (its
@@ -354,11 +354,28 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
         }
         if (FO) {
           // z face z0 + t of the group (a chunk's last face is the next one's first)
-          const int p = z0 + t;
-          const int f = (p == 0) ? 0 : (p == 16 ? 1 : (p == 8 && a.nf == 3 ? 2 : -1));
-          if (f >= 0 && (t >= 0 && (t < nzt || p == 16))) {
+          const int p = z0 + t, yx = tid;  // tid = y 16 + x
+          if constexpr (ZR <= 1) {
+            const int f = (p == 0) ? 0 : (p == 16 ? 1 : (p == 8 && a.nf == 3 ? 2 : -1));
+            if (f >= 0 && (t >= 0 && (t < nzt || p == 16))) {
 #pragma unroll
-            for (int n = 0; n < 5; ++n) gstore(FO + ((2 * a.nf + f) * 5 + n) * 256, (unsigned)(y * 16 + x) * (unsigned)sizeof(T), hn[n] + poison);
+              for (int n = 0; n < 5; ++n) gstore(FO + ((2 * a.nf + f) * 5 + n) * 256, (unsigned)yx * (unsigned)sizeof(T), hn[n] + poison);
+            }
+          } else {
+            // A run: the lower or mid face of plane t's group, and the upper
+            // face of the group below.
+            const long gstride = (long)gzs * (3 * a.nf * 5 * 256);
+            const int f = (t & 15) == 0 ? 0 : ((t & 15) == 8 && a.nf == 3 ? 2 : -1);
+            if (t >= 0 && t < nzt && f >= 0) {
+              T* Fg = FO + (t >> 4) * gstride + (2 * a.nf + f) * 5 * 256;
+#pragma unroll
+              for (int n = 0; n < 5; ++n) gstore(Fg + n * 256, (unsigned)yx * (unsigned)sizeof(T), hn[n] + poison);
+            }
+            if (t > 0 && f == 0) {
+              T* Fg = FO + ((t >> 4) - 1) * gstride + (2 * a.nf + 1) * 5 * 256;
+#pragma unroll
+              for (int n = 0; n < 5; ++n) gstore(Fg + n * 256, (unsigned)yx * (unsigned)sizeof(T), hn[n] + poison);
+            }
           }
         }
       } else if (FO && t >= 0 && t < nzt) {
@@ -366,10 +383,16 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
         if (q < 2 * a.nf * 16) {
           const bool d = q >= a.nf * 16;
           const int f = (q / 16) % a.nf, s = q % 16;
+          T* Fg = FO;
+          int zg = z0 + t;  // plane in its group
+          if constexpr (ZR > 1) {
+            Fg += (long)(t >> 4) * gzs * (3 * a.nf * 5 * 256);
+            zg = t & 15;
+          }
           const int fi = f == 0 ? -1 : (f == 1 ? 15 : 7);
           const V5<T> v = from_frame_d(lds5(sF2 + (d ? 5 * kF2 : 0), kF2, s * 17 + fi + 1), d);
 #pragma unroll
-          for (int n = 0; n < 5; ++n) gstore(FO + (((d ? 1 : 0) * a.nf + f) * 5 + n) * 256, (unsigned)((z0 + t) * 16 + s) * (unsigned)sizeof(T), v[n] + poison);
+          for (int n = 0; n < 5; ++n) gstore(Fg + (((d ? 1 : 0) * a.nf + f) * 5 + n) * 256, (unsigned)(zg * 16 + s) * (unsigned)sizeof(T), v[n] + poison);
         }
       }
     }

@@ -8,9 +8,9 @@
 namespace hy {
 namespace muscl_launch {
 
-template <int MODE, bool PPM, int RS, int WAVES, bool FAST, int ZR>
+template <int MODE, bool PPM, int RS, int WAVES, bool FAST, int ZR, bool FLUX>
 hipError_t launch_zr(const FusedArgs<float>& a, int grid, hipStream_t st) {
-  auto k = muscl::muscl_kernel<float, PPM, RS, WAVES, MODE, FAST, ZR>;
+  auto k = muscl::muscl_kernel<float, PPM, RS, WAVES, MODE, FAST, ZR, FLUX>;
   const size_t shm = muscl::kLdsBytes(sizeof(float));
   static std::atomic<unsigned long long> lds_set{0};
   const hipError_t e = raise_lds_limit((const void*)k, shm, lds_set);
@@ -23,16 +23,23 @@ hipError_t launch_zr(const FusedArgs<float>& a, int grid, hipStream_t st) {
 // specialization with two workgroups per CU (zrun_built).
 template <int MODE, bool PPM, int RS, int WAVES, bool FAST>
 hipError_t launch_one(const FusedArgs<float>& a, int grid, hipStream_t st) {
+  const bool flux = has_flux(a);
   if (a.zsplit > 1) {
-    if constexpr (WAVES == 4) return launch_zr<MODE, PPM, RS, WAVES, FAST, 0>(a, grid, st);
+    if constexpr (WAVES == 4)
+      return flux ? launch_zr<MODE, PPM, RS, WAVES, FAST, 0, true>(a, grid, st) : launch_zr<MODE, PPM, RS, WAVES, FAST, 0, false>(a, grid, st);
     return hipErrorInvalidValue;
   }
   if constexpr (WAVES == 4 && FAST && PPM) {
-    if (a.zrun == 2) return launch_zr<MODE, PPM, RS, WAVES, FAST, 2>(a, grid, st);
-    if (a.zrun == 4) return launch_zr<MODE, PPM, RS, WAVES, FAST, 4>(a, grid, st);
+    if (a.zrun == 2)
+      return flux ? launch_zr<MODE, PPM, RS, WAVES, FAST, 2, true>(a, grid, st) : launch_zr<MODE, PPM, RS, WAVES, FAST, 2, false>(a, grid, st);
+    if (a.zrun == 4)
+      return flux ? launch_zr<MODE, PPM, RS, WAVES, FAST, 4, true>(a, grid, st) : launch_zr<MODE, PPM, RS, WAVES, FAST, 4, false>(a, grid, st);
   }
   if (a.zrun != 1) return hipErrorInvalidValue;
-  return launch_zr<MODE, PPM, RS, WAVES, FAST, 1>(a, grid, st);
+  if constexpr (WAVES == 4) {
+    if (!flux) return launch_zr<MODE, PPM, RS, WAVES, FAST, 1, false>(a, grid, st);
+  }
+  return launch_zr<MODE, PPM, RS, WAVES, FAST, 1, true>(a, grid, st);
 }
 
 template <int MODE, int WAVES, bool FAST>

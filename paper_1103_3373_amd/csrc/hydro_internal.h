@@ -78,7 +78,7 @@ struct FusedArgs {
   // box of its own whose ghost cells the second stage reads from neighbours.
   T* wstar;
   int wstar_box;
-  // CTU on one periodic box (seg0, no flux output): a workgroup marches
+  // One periodic box (seg0): a workgroup marches
   // through zrun z-consecutive groups of one (gx, gy) column in one pass, so
   // the work items are n_groups / zrun runs (ngz a multiple of zrun).  1
   // everywhere else.
@@ -88,6 +88,10 @@ struct FusedArgs {
   // predictor and the solver have their own.
   int zsplit;
 };
+
+// Whether a launch may store face fluxes (the host does not see the pointers of
+// a segment table).
+template <typename T> inline bool has_flux(const FusedArgs<T>& a) { return a.segs || a.seg0.flux; }
 
 // Tile depths (groups per z-run) built for the fused kernels: 1 always; 2
 // and 4 for the FP32 specialization of the production configuration (van

@@ -389,7 +389,7 @@ def set_launch_shape(spec: Spec, grid: int, variant: int, zrun: int = 0) -> None
 
 def get_launch_shape(spec: Spec, shape) -> tuple:
     """(grid, variant, zrun) that step_box uses for spec on a box of
-    shape = (nx, ny, nz) without flux output."""
+    shape = (nx, ny, nz), with flux output or without."""
     a, b, c = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
     nx, ny, nz = shape
     _check("hydro_get_launch_shape", lib().hydro_get_launch_shape(ctypes.byref(spec), int(nx), int(ny), int(nz),
