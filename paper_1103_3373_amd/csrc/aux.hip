@@ -602,114 +602,152 @@ __device__ __forceinline__ int fine_owner(const int* fmap, int nf, int ngf, int 
 // side, += on its - side, in the order x, y, z and -, +.  No contraction:
 // the same FP64 expression as a plain evaluation.
 //
-// One 64-thread workgroup per face of a fine group, one thread per coarse
-// cell just outside that face (8 x 8).  A cell next to several refined
-// patches is visited from several faces; only the face of its first covered
-// neighbour in the order above processes it, applying all of its
-// corrections in that order, so every cell is written by one thread.
+// Restriction.  A covered coarse cell becomes the mean of its 8 children.
+//
+// One 512-thread workgroup per fine group: a thread per covered cell (8^3)
+// for the restriction, and waves 0 to 5 a face each, a thread per coarse cell
+// just outside it (8 x 8).  The two write disjoint cells (covered, uncovered).
+// A cell next to several refined patches is visited from several faces; only
+// the face of its first covered neighbour in the order above processes it,
+// applying all of its corrections in that order, so every cell is written by
+// one thread.  Only the group that the map names at its position writes.
+//
+// A face's cells lie in one coarse patch, so all that is looked up in the map
+// is uniform: the patch itself and its four neighbours beside the face.  Both
+// parts wait for memory (a chain of layout, map, fluxes against a stream of
+// fine cells), so they share a launch and the fine cells are requested before
+// the chain is followed.  6144 groups in a 256^3 box, FP32: 330 us in two
+// launches (refluxing 153, restriction 177), 290 in one, which moves 1.2 GB
+// (counted; rows of 8 cells of 16, single cells beside x faces): 4.2 TB/s.
+template <typename T> struct Reflux {
+  const T* cflux;
+  const T* fflux;
+  double dtdh;
+};
+// Adds the correction of face q = 2 d + (fine side > 0) of cell c (in group
+// G) from fine group F with layout entry o.
 template <typename T>
-__global__ void __launch_bounds__(64) reflux_kernel(T* __restrict__ U, int n, const T* __restrict__ cflux,
-                                                    const int* __restrict__ fmap, int nf, const T* __restrict__ fflux,
-                                                    const int4* __restrict__ flayout, double dtdh) {
+__device__ __forceinline__ void reflux_face(double (&u)[5], const Reflux<T>& R, long long G, const int (&c)[3], int d,
+                                            int side, int F, const int4 o) {
 #pragma clang fp contract(off)
-  const int F0 = blockIdx.x / 6, face = blockIdx.x % 6;
-  const int dF = face >> 1, sF = (face & 1) ? 1 : -1;  // the fine group's face: axis and side
+  // transverse coordinates (slow, fast) of a d-face: x (z, y), y (z, x), z (y, x)
+  const int cd = d == 0 ? c[0] : (d == 1 ? c[1] : c[2]);
+  const int cs = d == 2 ? c[1] : c[2], cf = d == 0 ? c[1] : c[0];
+  const int os = d == 2 ? o.z : o.w, of = d == 0 ? o.z : o.y;
+  const int ld = cd & 15;
+  const int slot = side > 0 ? (ld == 15 ? 1 : (ld == 7 ? 2 : -1)) : (ld == 0 ? 0 : (ld == 8 ? 2 : -1));
+  if (slot < 0) return;  // cannot happen: fine groups cover whole coarse patches
+  const int fs0 = 2 * (cs - (os >> 1)), ff0 = 2 * (cf - (of >> 1));
+  if (fs0 < 0 || fs0 > 14 || ff0 < 0 || ff0 > 14) return;  // layout disagrees with the map
+  const int fslot = side > 0 ? 0 : 1;  // F's face towards this cell
+  const double sg = side > 0 ? -1.0 : 1.0;
+  const T* cp = R.cflux + ((G * 3 + d) * 3 + slot) * 1280 + (cs & 15) * 16 + (cf & 15);
+  const T* fp = R.fflux + (((long long)F * 3 + d) * 2 + fslot) * 1280 + fs0 * 16 + ff0;
+#pragma unroll
+  for (int v = 0; v < 5; ++v) {
+    const double Fc = (double)cp[v * 256];
+    double Ff = 0.0;
+    Ff += (double)fp[v * 256];
+    Ff += (double)fp[v * 256 + 1];
+    Ff += (double)fp[v * 256 + 16];
+    Ff += (double)fp[v * 256 + 17];
+    Ff *= 0.25;
+    u[v] += sg * R.dtdh * (Ff - Fc);
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(512) amr_correct_kernel(T* __restrict__ U, int n, const T* __restrict__ cflux,
+                                                          const T* __restrict__ fine, const int4* __restrict__ flayout,
+                                                          const int* __restrict__ fmap, int nf,
+                                                          const T* __restrict__ fflux, double dtdh) {
+#pragma clang fp contract(off)
+  const int F0 = blockIdx.x, tid = threadIdx.x;
+  T r[5][8];
+  {
+    const int i = tid & 7, j = (tid >> 3) & 7, k = tid >> 6;
+    const T* f = fine + (long long)F0 * 5 * 4096 + (2 * k * 16 + 2 * j) * 16 + 2 * i;
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) r[v][q] = f[v * 4096 + (q >> 2) * 256 + ((q >> 1) & 1) * 16 + (q & 1)];
+  }
+  asm volatile("" ::: "memory");  // the loads stay ahead of the chain below
   const int4 o0 = flayout[F0];
   const int nfine = 2 * n, ng = n >> 4, ngf = n >> 3;
   if (o0.y < 0 || o0.z < 0 || o0.w < 0 || o0.y >= nfine || o0.z >= nfine || o0.w >= nfine ||
       ((o0.y | o0.z | o0.w) & 15))
     return;
-  const int c0[3] = {o0.y >> 1, o0.z >> 1, o0.w >> 1};
-  if (fine_owner(fmap, nf, ngf, c0[0], c0[1], c0[2]) != F0) return;
-  // The coarse cell a outside this face; from a, the refined patch lies on
-  // side -sF along dF.
-  const int e1 = dF == 0 ? 1 : 0, e2 = dF == 2 ? 1 : 2;
-  int c[3];
-  c[dF] = sF < 0 ? c0[dF] - 1 : c0[dF] + 8;
-  c[dF] += c[dF] < 0 ? n : 0;
-  c[dF] -= c[dF] >= n ? n : 0;
-  c[e1] = c0[e1] + (threadIdx.x & 7);
-  c[e2] = c0[e2] + (threadIdx.x >> 3);
-  if (fine_owner(fmap, nf, ngf, c[0], c[1], c[2]) >= 0) return;  // covered: restriction sets it
-  int owners[6];
-  int first = -1;
-  for (int q = 0; q < 6; ++q) {
-    const int d = q >> 1, side = (q & 1) ? 1 : -1;
-    int b[3] = {c[0], c[1], c[2]};
-    b[d] += side;
-    b[d] += b[d] < 0 ? n : 0;
-    b[d] -= b[d] >= n ? n : 0;
-    owners[q] = fine_owner(fmap, nf, ngf, b[0], b[1], b[2]);
-    if (owners[q] >= 0 && first < 0) first = q;
-  }
-  if (first != dF * 2 + (sF < 0 ? 1 : 0)) return;  // another face processes this cell
-  const long long G = ((long long)(c[2] >> 4) * ng + (c[1] >> 4)) * ng + (c[0] >> 4);
-  const int l = ((c[2] & 15) * 16 + (c[1] & 15)) * 16 + (c[0] & 15);
-  const int loc[3] = {c[0] & 15, c[1] & 15, c[2] & 15};
-  double u[5];
+  const int p0[3] = {o0.y >> 4, o0.z >> 4, o0.w >> 4};  // coarse patch of 8^3 cells
+  if (fine_owner(fmap, nf, ngf, 8 * p0[0], 8 * p0[1], 8 * p0[2]) != F0) return;
+
+  const int face = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (face < 6) {
+    const int dF = face >> 1, sF = (face & 1) ? 1 : -1;  // the fine group's face: axis and side
+    // the patch outside this face, and a lane's cell in it
+    int p[3] = {p0[0] + (dF == 0 ? sF : 0), p0[1] + (dF == 1 ? sF : 0), p0[2] + (dF == 2 ? sF : 0)};
 #pragma unroll
-  for (int v = 0; v < 5; ++v) u[v] = (double)U[(G * 5 + v) * 4096 + l];
-  for (int q = 0; q < 6; ++q) {
-    const int F = owners[q];
-    if (F < 0) continue;
-    const int d = q >> 1, side = (q & 1) ? 1 : -1;
-    // transverse coordinates (slow, fast) of a d-face: x (z, y), y (z, x), z (y, x)
-    const int ts = d == 2 ? 1 : 2, tf = d == 0 ? 1 : 0;
-    const int slot = side > 0 ? (loc[d] == 15 ? 1 : (loc[d] == 7 ? 2 : -1)) : (loc[d] == 0 ? 0 : (loc[d] == 8 ? 2 : -1));
-    if (slot < 0) continue;  // cannot happen: fine groups cover whole coarse patches
-    const int4 o = flayout[F];
-    const int fo[3] = {o.y, o.z, o.w};
-    const int fs0 = 2 * (c[ts] - (fo[ts] >> 1)), ff0 = 2 * (c[tf] - (fo[tf] >> 1));
-    if (fs0 < 0 || fs0 > 14 || ff0 < 0 || ff0 > 14) continue;  // layout disagrees with the map
-    const int fslot = side > 0 ? 0 : 1;  // F's face towards this cell
-    const double sg = side > 0 ? -1.0 : 1.0;
+    for (int d = 0; d < 3; ++d) {
+      p[d] += p[d] < 0 ? ngf : 0;
+      p[d] -= p[d] >= ngf ? ngf : 0;
+    }
+    auto owner = [&](int a, int b, int e) {
+      const int o = fmap[((long long)e * ngf + b) * ngf + a];
+      return (o >= 0 && o < nf) ? o : -1;
+    };
+    // Transverse neighbours of the patch, axes e1 < e2, sides -, +.
+    const int e1 = dF == 0 ? 1 : 0, e2 = dF == 2 ? 1 : 2;
+    int nb[4];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      const double Fc = (double)cflux[((((G * 3 + d) * 3 + slot) * 5 + v) * 16 + loc[ts]) * 16 + loc[tf]];
-      const T* f = fflux + ((((long long)F * 3 + d) * 2 + fslot) * 5 + v) * 256;
-      double Ff = 0.0;
-      Ff += (double)f[fs0 * 16 + ff0];
-      Ff += (double)f[fs0 * 16 + ff0 + 1];
-      Ff += (double)f[(fs0 + 1) * 16 + ff0];
-      Ff += (double)f[(fs0 + 1) * 16 + ff0 + 1];
-      Ff *= 0.25;
-      u[v] += sg * dtdh * (Ff - Fc);
+    for (int k = 0; k < 4; ++k) {
+      const int e = k < 2 ? e1 : e2, sd = (k & 1) ? 1 : -1;
+      int b[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        b[d] = p[d] + (d == e ? sd : 0);
+        b[d] += b[d] < 0 ? ngf : 0;
+        b[d] -= b[d] >= ngf ? ngf : 0;
+      }
+      nb[k] = owner(b[0], b[1], b[2]);
+    }
+    if (owner(p[0], p[1], p[2]) < 0) {  // else covered: restriction sets it
+      const int l1 = tid & 7, l2 = (tid >> 3) & 7;
+      const int ln = sF < 0 ? 7 : 0;  // along dF, next to the refined patch
+      const int c[3] = {8 * p[0] + (dF == 0 ? ln : l1), 8 * p[1] + (dF == 1 ? ln : (dF == 0 ? l1 : l2)),
+                        8 * p[2] + (dF == 2 ? ln : l2)};
+      // Covered neighbours beside the face, per lane: e1 -, +, e2 -, +.
+      const int own[4] = {l1 == 0 ? nb[0] : -1, l1 == 7 ? nb[1] : -1, l2 == 0 ? nb[2] : -1, l2 == 7 ? nb[3] : -1};
+      // An axis before dF: that face processes the cell.
+      const bool mine = !((e1 < dF && (own[0] >= 0 || own[1] >= 0)) || (e2 < dF && (own[2] >= 0 || own[3] >= 0)));
+      if (mine) {
+        const Reflux<T> R{cflux, fflux, dtdh};
+        const long long G = ((long long)(c[2] >> 4) * ng + (c[1] >> 4)) * ng + (c[0] >> 4);
+        T* up = U + G * 5 * 4096 + ((c[2] & 15) * 16 + (c[1] & 15)) * 16 + (c[0] & 15);
+        double u[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) u[v] = (double)up[v * 4096];
+        reflux_face(u, R, G, c, dF, -sF, F0, o0);  // from the cell, the patch lies on side -sF
+        // and the faces after it in the order
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int e = k < 2 ? e1 : e2;
+          if (e > dF && nb[k] >= 0 && own[k] >= 0) reflux_face(u, R, G, c, e, (k & 1) ? 1 : -1, nb[k], flayout[nb[k]]);
+        }
+#pragma unroll
+        for (int v = 0; v < 5; ++v) up[v * 4096] = (T)u[v];
+      }
     }
   }
-#pragma unroll
-  for (int v = 0; v < 5; ++v) U[(G * 5 + v) * 4096 + l] = (T)u[v];
-}
 
-// Restriction: one workgroup per fine group, one thread per covered coarse
-// cell (8^3); only the group that the map names at its position writes.
-template <typename T>
-__global__ void __launch_bounds__(512) restrict_kernel(T* __restrict__ U, int n, const T* __restrict__ fine,
-                                                       const int4* __restrict__ flayout, const int* __restrict__ fmap,
-                                                       int nf) {
-#pragma clang fp contract(off)
-  const int F = blockIdx.x;
-  const int4 o = flayout[F];
-  const int nfine = 2 * n;
-  if (o.y < 0 || o.z < 0 || o.w < 0 || o.y >= nfine || o.z >= nfine || o.w >= nfine || ((o.y | o.z | o.w) & 15))
-    return;
-  const int cx0 = o.y >> 1, cy0 = o.z >> 1, cz0 = o.w >> 1;
-  if (fine_owner(fmap, nf, n >> 3, cx0, cy0, cz0) != F) return;
-  const int i = threadIdx.x & 7, j = (threadIdx.x >> 3) & 7, k = threadIdx.x >> 6;
-  const int cx = cx0 + i, cy = cy0 + j, cz = cz0 + k;
-  const int ng = n >> 4;
-  const long long G = ((long long)(cz >> 4) * ng + (cy >> 4)) * ng + (cx >> 4);
-  const int l = ((cz & 15) * 16 + (cy & 15)) * 16 + (cx & 15);
+  const int cx = 8 * p0[0] + (tid & 7), cy = 8 * p0[1] + ((tid >> 3) & 7), cz = 8 * p0[2] + (tid >> 6);
+  T* up = U + (((long long)(cz >> 4) * ng + (cy >> 4)) * ng + (cx >> 4)) * 5 * 4096 +
+          ((cz & 15) * 16 + (cy & 15)) * 16 + (cx & 15);
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
-    const T* f = fine + ((long long)F * 5 + v) * 4096;
     double s = 0.0;
 #pragma unroll
-    for (int dz = 0; dz < 2; ++dz)
-#pragma unroll
-      for (int dy = 0; dy < 2; ++dy)
-#pragma unroll
-        for (int dx = 0; dx < 2; ++dx) s += (double)f[((2 * k + dz) * 16 + 2 * j + dy) * 16 + 2 * i + dx];
-    U[(G * 5 + v) * 4096 + l] = (T)(0.125 * s);
+    for (int q = 0; q < 8; ++q) s += (double)r[v][q];
+    up[v * 4096] = (T)(0.125 * s);
   }
 }
 
@@ -717,11 +755,8 @@ template <typename T>
 hipError_t launch_amr_correct(T* U, int n, const T* cflux, const T* fine, const int* flayout, int nf,
                               const int* fmap, const T* fflux, double dtdh, hipStream_t st) {
   if (nf == 0) return hipSuccess;
-  reflux_kernel<T><<<dim3((unsigned)(6 * (long long)nf)), dim3(64), 0, st>>>(U, n, cflux, fmap, nf, fflux,
-                                                                             (const int4*)flayout, dtdh);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  restrict_kernel<T><<<dim3((unsigned)nf), dim3(512), 0, st>>>(U, n, fine, (const int4*)flayout, fmap, nf);
+  amr_correct_kernel<T><<<dim3((unsigned)nf), dim3(512), 0, st>>>(U, n, cflux, fine, (const int4*)flayout, fmap, nf,
+                                                                 fflux, dtdh);
   return hipGetLastError();
 }
 template hipError_t launch_amr_correct<float>(float*, int, const float*, const float*, const int*, int, const int*,
