@@ -26,22 +26,20 @@ CFLAGS = [
 ]
 # Per-file additions.  The CTU kernels build with the AMDGPU scheduler's
 # register-pressure trackers that follow the register allocator's own
-# accounting.  For
-# the FP32 HLLC/HLLE CTU kernel of the current source they give 1 spilled
-# VGPR and 1.150 ms at 256^3, against 30 and 1.186 ms with the default
-# scheduler; adding the max-ILP strategy (which once paid off for this file)
-# now gives 26 spills and 1.154 ms, and max-ILP alone 1.272 ms.
+# accounting.  256^3 box steps, us (FP32, PPM): default, trackers, max-ILP,
+# max-memory-clause and iterative-minreg schedules:
+#   CTU/HLLC            1226, 1122, 1262, 1270, 1277
+#   CTU/Roe             1538, 1707, 1696, 1702, 1690
+#   MHM/HLLC             845,  844,  836,  855,  965
+#   MHM/HLLC + fluxes    869,  852,  869,  879,  995
+#   MHM/Roe + fluxes     947,  911,  952,  950, 1075
+#   VL/HLLC             1010,  964, 1002, 1013, 1167
 EXTRA = {
     "fused_ctu_f32.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"],
-    # MHM and the VL second stage share a kernel template but not their best
-    # schedule: the trackers make the VL step (predictor and second stage)
-    # 2.8% faster and leave MHM unchanged; max-ILP makes MHM 1.1% faster and
-    # the VL step 1% slower.
+    # VL and MHM with the flux code take the trackers, MHM without it max-ILP,
+    # the FP32 Roe CTU file (fused_ctu_f32_roe.hip) the default.
     "fused_muscl_f32.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"],
     "fused_muscl_f32_mhm.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-    # The FP32 Roe CTU file (fused_ctu_f32_roe.hip) builds with the default
-    # scheduler: 1.456 ms per 256^3 box step against 1.504 ms with the
-    # trackers and 1.549 ms with max-ILP.
     "fused_ctu_f64.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"],
 }
 

@@ -1,5 +1,6 @@
-// Instantiations of the fused VL-second-stage kernel and the VL predictor for
-// float; MHM's are in their own file (other scheduler options).
+// Instantiations of the fused VL-second-stage kernel, the VL predictor and the
+// MHM kernel with flux code for float; MHM's without are in their own file
+// (other scheduler options).
 #include "fused_muscl_launch.hpp"
 #include "fused_vlpred.hpp"
 
@@ -9,8 +10,12 @@ hipError_t launch_mhm_f32(const FusedArgs<float>& a, int recon, int riemann, con
 
 hipError_t launch_muscl_f32(const FusedArgs<float>& a, int mode, int recon, int riemann, const FusedCfg& cfg,
                              hipStream_t st) {
-  if (mode == 0) return launch_mhm_f32(a, recon, riemann, cfg, st);
-  return muscl_launch::launch_mode<1>(a, recon, riemann, cfg, st);
+  const bool flux = muscl_launch::with_flux_code(a, cfg);
+  if (mode == 0)
+    return flux ? muscl_launch::launch_mode<0, true>(a, recon, riemann, cfg, st)
+                : launch_mhm_f32(a, recon, riemann, cfg, st);
+  return flux ? muscl_launch::launch_mode<1, true>(a, recon, riemann, cfg, st)
+              : muscl_launch::launch_mode<1, false>(a, recon, riemann, cfg, st);
 }
 
 template <int G, int RS>

@@ -1,6 +1,6 @@
 // Launch helpers of the fused MHM / VL-second-stage kernel for float, shared
-// by the two files that instantiate it (MHM and the VL second stage build
-// with different scheduler options).
+// by the two files that instantiate it (MHM without the flux code builds with
+// other scheduler options than the rest).
 #pragma once
 
 #include "fused_muscl.hpp"
@@ -21,51 +21,48 @@ hipError_t launch_zr(const FusedArgs<float>& a, int grid, hipStream_t st) {
 
 // Tile depths 2 and 4 exist for the PPM van Leer / characteristic
 // specialization with two workgroups per CU (zrun_built).
-template <int MODE, bool PPM, int RS, int WAVES, bool FAST>
+template <int MODE, bool PPM, int RS, int WAVES, bool FAST, bool FLUX>
 hipError_t launch_one(const FusedArgs<float>& a, int grid, hipStream_t st) {
-  const bool flux = has_flux(a);
   if (a.zsplit > 1) {
-    if constexpr (WAVES == 4)
-      return flux ? launch_zr<MODE, PPM, RS, WAVES, FAST, 0, true>(a, grid, st) : launch_zr<MODE, PPM, RS, WAVES, FAST, 0, false>(a, grid, st);
+    if constexpr (WAVES == 4) return launch_zr<MODE, PPM, RS, WAVES, FAST, 0, FLUX>(a, grid, st);
     return hipErrorInvalidValue;
   }
   if constexpr (WAVES == 4 && FAST && PPM) {
-    if (a.zrun == 2)
-      return flux ? launch_zr<MODE, PPM, RS, WAVES, FAST, 2, true>(a, grid, st) : launch_zr<MODE, PPM, RS, WAVES, FAST, 2, false>(a, grid, st);
-    if (a.zrun == 4)
-      return flux ? launch_zr<MODE, PPM, RS, WAVES, FAST, 4, true>(a, grid, st) : launch_zr<MODE, PPM, RS, WAVES, FAST, 4, false>(a, grid, st);
+    if (a.zrun == 2) return launch_zr<MODE, PPM, RS, WAVES, FAST, 2, FLUX>(a, grid, st);
+    if (a.zrun == 4) return launch_zr<MODE, PPM, RS, WAVES, FAST, 4, FLUX>(a, grid, st);
   }
   if (a.zrun != 1) return hipErrorInvalidValue;
-  if constexpr (WAVES == 4) {
-    if (!flux) return launch_zr<MODE, PPM, RS, WAVES, FAST, 1, false>(a, grid, st);
-  }
-  return launch_zr<MODE, PPM, RS, WAVES, FAST, 1, true>(a, grid, st);
+  return launch_zr<MODE, PPM, RS, WAVES, FAST, 1, FLUX>(a, grid, st);
 }
 
-template <int MODE, int WAVES, bool FAST>
+template <int MODE, int WAVES, bool FAST, bool FLUX>
 hipError_t launch_wf(const FusedArgs<float>& a, int recon, int riemann, int grid, hipStream_t st) {
   if (recon == 1) {
-    if (riemann == 0) return launch_one<MODE, true, 0, WAVES, FAST>(a, grid, st);
-    if (riemann == 1) return launch_one<MODE, true, 1, WAVES, FAST>(a, grid, st);
-    return launch_one<MODE, true, 2, WAVES, FAST>(a, grid, st);
+    if (riemann == 0) return launch_one<MODE, true, 0, WAVES, FAST, FLUX>(a, grid, st);
+    if (riemann == 1) return launch_one<MODE, true, 1, WAVES, FAST, FLUX>(a, grid, st);
+    return launch_one<MODE, true, 2, WAVES, FAST, FLUX>(a, grid, st);
   }
-  if (riemann == 0) return launch_one<MODE, false, 0, WAVES, FAST>(a, grid, st);
-  if (riemann == 1) return launch_one<MODE, false, 1, WAVES, FAST>(a, grid, st);
-  return launch_one<MODE, false, 2, WAVES, FAST>(a, grid, st);
+  if (riemann == 0) return launch_one<MODE, false, 0, WAVES, FAST, FLUX>(a, grid, st);
+  if (riemann == 1) return launch_one<MODE, false, 1, WAVES, FAST, FLUX>(a, grid, st);
+  return launch_one<MODE, false, 2, WAVES, FAST, FLUX>(a, grid, st);
 }
 
-template <int MODE, int WAVES>
+template <int MODE, int WAVES, bool FLUX>
 hipError_t launch_w(const FusedArgs<float>& a, int recon, int riemann, int grid, hipStream_t st) {
-  if (a.limiter == 1 && a.charlim == 1) return launch_wf<MODE, WAVES, true>(a, recon, riemann, grid, st);
-  return launch_wf<MODE, WAVES, false>(a, recon, riemann, grid, st);
+  if (a.limiter == 1 && a.charlim == 1) return launch_wf<MODE, WAVES, true, FLUX>(a, recon, riemann, grid, st);
+  return launch_wf<MODE, WAVES, false, FLUX>(a, recon, riemann, grid, st);
 }
 
-// Every specialization of one mode (0 MHM, 1 VL second stage).
-template <int MODE>
+// Every specialization of one mode (0 MHM, 1 VL second stage) with the flux
+// code or without.  One workgroup per CU has registers enough for it: that
+// variant is built with it only.
+template <int MODE, bool FLUX>
 hipError_t launch_mode(const FusedArgs<float>& a, int recon, int riemann, const FusedCfg& cfg, hipStream_t st) {
-  if (cfg.waves == 4) return launch_w<MODE, 4>(a, recon, riemann, cfg.grid, st);
-  return launch_w<MODE, 2>(a, recon, riemann, cfg.grid, st);
+  if (cfg.waves == 4) return launch_w<MODE, 4, FLUX>(a, recon, riemann, cfg.grid, st);
+  if constexpr (FLUX) return launch_w<MODE, 2, true>(a, recon, riemann, cfg.grid, st);
+  return hipErrorInvalidValue;
 }
+inline bool with_flux_code(const FusedArgs<float>& a, const FusedCfg& cfg) { return has_flux(a) || cfg.waves != 4; }
 
 }  // namespace muscl_launch
 }  // namespace hy
