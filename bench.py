@@ -573,7 +573,7 @@ def main():
         plain = {"path": "plain per-group FP64 (one workgroup per group, global temporaries)",
                  "ms_per_solve": round(pms, 3), "cell_updates_per_s": cells / (pms * 1e-3),
                  "speedup_of_fused_solve": round(pms / kern_avg, 2)}
-        # The exact Riemann solver (plain path only) on the same input, FP64.
+        # The exact Riemann solver (fused groups path) on the same input, FP64.
         H.get_diag(reset=True)
         pe[0].record(stream)
         H.solve_groups(gh64, out64, None, dt=dt0, dh=dh, gamma=gamma, scheme=H.CTU, recon=H.PPM, riemann=H.EXACT,
