@@ -101,10 +101,15 @@ template <typename T> HY_DEV V5<T> other_frame_d(const V5<T>& v, bool d) {
   return r;
 }
 
-// A per-lane value that the compiler takes as new here: what a run's flux
-// stores form from it is not carried in registers through the plane loop
-// (256^3 with flux in runs of 4: HLLC 1244 -> 1223 us, Roe 1676 -> 1655; MHM,
-// with registers to spare, and single groups gain nothing).
+// A per-lane value that the compiler takes as new here.  Each phase of a plane
+// decodes its tasks from the thread number; taken as an invariant of the plane
+// loop, the decoded indices and addresses of every phase would stay in
+// registers through all the others, and the FP32 kernels spill at two
+// workgroups per CU (scratch a lane at tile depth 4: HLLC 28 -> 12 B, with
+// fluxes 36 -> 24; Roe 124 -> 104).  The phases' few integer instructions cost
+// less: 256^3 box step HLLC 1126 -> 1103 us, with fluxes 1223 -> 1177; Roe
+// 1540 -> 1509 and 1656 -> 1636; 256 x 128 x 128 cells of ghosted groups with
+// fluxes HLLC 345 -> 326, Roe 459 -> 442; a batched box 328 -> 313.
 HY_DEV int here(int v) {
   asm volatile("" : "+v"(v));
   return v;
@@ -148,6 +153,11 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
 
   const int tid = threadIdx.x;
   const Column<int> col = column_of<G>(tid);
+  // the thread number for a phase's task decode
+  auto lane = [&]() -> int {
+    if constexpr (sizeof(T) == 4 && RS != 3) return here(tid);
+    else return tid;
+  };
   const int pcol = (col.y + G) * N + (col.x + G);  // primitive plane index, lab
   const int qcol = (col.x + G) * N + (col.y + G);  // the same cell in the transposed plane
   const int sqc = (col.y + 1) * 18 + (col.x + 1);  // 18x18 square index (cross columns)
@@ -326,7 +336,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
       } else if (!warming) {
         // Ring corners and outer columns (column ids 320 .. nCols-1), strided
         // over the threads that own no cross column.
-        for (int c = tid; c < nCols; c += NT - 320) {
+        for (int c = lane(); c < nCols; c += NT - 320) {
           const Column<int> oc = column_of<G>(c);
           ColumnReader<T, G> orr = rd;  // z part of the group
           orr.off = sOC[c - 320];
@@ -343,7 +353,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
       __syncthreads();
 
       // ---- B: limited slopes along x and y of plane t ----------------------
-      for (int q = tid; q < 2 * nS; q += NT) {
+      for (int q = lane(); q < 2 * nS; q += NT) {
         const bool d = q >= nS;
         const int r = d ? q - nS : q;
         const int aa = r % wS + a0S, b = r / wS - 1;
@@ -355,7 +365,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
       __syncthreads();
 
       // ---- C: traced x and y face states of plane t (frame of d) -----------
-      for (int q = tid; q < 2 * kSQ; q += NT) {
+      for (int q = lane(); q < 2 * kSQ; q += NT) {
         const bool d = q >= kSQ;
         const int r = d ? q - kSQ : q;
         const int aa = r % 18 - 1, b = r / 18 - 1;
@@ -390,7 +400,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
 
       // ---- D: first-set Riemann solves in x and y, stored in the other
       //         direction's frame (where they are used) ----------------------
-      for (int q = tid; q < 2 * kF1; q += NT) {
+      for (int q = lane(); q < 2 * kF1; q += NT) {
         const bool d = q >= kF1;
         const int r = d ? q - kF1 : q;
         const int i = r % 17 - 1, b = r / 17 - 1;  // face between cells i and i+1 of row b
@@ -407,7 +417,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
       //         z correction of plane t and H(t-1/2) (interior columns) ----
       V5<T> hn;
       if (interior) {
-        const int x = col.x, y = col.y;
+        const int yx = lane(), x = yx & 15, y = yx >> 4;
         // x fluxes (stored in the y frame) at x -+ 1/2, y fluxes (stored in
         // the lab order) at y -+ 1/2.
         V5<T> dF = sub5(lds5(sF1, kF1, (y + 1) * 17 + x + 1), lds5(sF1, kF1, (y + 1) * 17 + x));
@@ -427,7 +437,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
         zcp = cp;
       }
       if (t >= 0 && t < nzt) {
-        for (int q = NT - 1 - tid; q < 2 * kF2; q += NT) {
+        for (int q = NT - 1 - lane(); q < 2 * kF2; q += NT) {
           const bool d = q >= kF2;
           const int r = d ? q - kF2 : q;
           const int i = r % 17 - 1, b = r / 17;  // face between cells i and i+1 of row b
@@ -477,7 +487,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
         }
         if (FO) {
           // z face z0 + t of the group (a chunk's last face is the next one's first)
-          const int p = z0 + t, yx = ZR > 1 ? here(tid) : tid;  // tid = y 16 + x
+          const int p = z0 + t, yx = lane();  // y 16 + x
           if constexpr (ZR <= 1) {
             const int f = (p == 0) ? 0 : (p == 16 ? 1 : (p == 8 && a.nf == 3 ? 2 : -1));
             if (f >= 0 && (t >= 0 && (t < nzt || p == 16))) {
@@ -502,7 +512,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
           }
         }
       } else if (FO && t >= 0 && t < nzt) {
-        const int q = (ZR > 1 ? here(tid) : tid) - 256;
+        const int q = lane() - 256;
         if (q < 2 * a.nf * 16) {
           const bool d = q >= a.nf * 16;
           const int f = (q / 16) % a.nf, s = q % 16;
