@@ -151,6 +151,23 @@ HY_DEV long long uni(long long v) {
 HY_DEV double uni(double v) { return __longlong_as_double(uni(__double_as_longlong(v))); }
 template <typename P> HY_DEV P* uni(P* p) { return reinterpret_cast<P*>(uni((long long)(uintptr_t)p)); }
 
+// A per-lane value that the compiler takes as new here.  Each phase of a plane
+// decodes its tasks from the thread number; taken as an invariant of the plane
+// loop, the decoded indices and addresses of every phase would stay in
+// registers through all the others, and the FP32 kernels spill at two
+// workgroups per CU (scratch a lane at tile depth 4: HLLC 28 -> 12 B, with
+// fluxes 36 -> 24; Roe 124 -> 104).  The phases' few integer instructions cost
+// less: 256^3 CTU box step HLLC 1126 -> 1103 us, with fluxes 1223 -> 1177; Roe
+// 1540 -> 1509 and 1656 -> 1636; 256 x 128 x 128 cells of ghosted groups with
+// fluxes HLLC 345 -> 326, Roe 459 -> 442; a batched box 328 -> 313.  MHM and VL
+// take it with the flux code (256^3 with fluxes MHM/Roe 914 -> 889, VL/Roe
+// 1321 -> 1297; a batched box MHM/HLLC 230 -> 227, MHM/Roe 245 -> 239), not
+// without: HLLC does not spill there (838 -> 845).
+HY_DEV int here(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // Global store / load at a uniform base plus a per-lane byte offset (the
 // base + 32-bit offset addressing form of the memory instructions).
 template <typename T> HY_DEV void gstore(T* base, unsigned byte_off, T v) {

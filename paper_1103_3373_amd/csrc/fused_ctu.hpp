@@ -101,20 +101,6 @@ template <typename T> HY_DEV V5<T> other_frame_d(const V5<T>& v, bool d) {
   return r;
 }
 
-// A per-lane value that the compiler takes as new here.  Each phase of a plane
-// decodes its tasks from the thread number; taken as an invariant of the plane
-// loop, the decoded indices and addresses of every phase would stay in
-// registers through all the others, and the FP32 kernels spill at two
-// workgroups per CU (scratch a lane at tile depth 4: HLLC 28 -> 12 B, with
-// fluxes 36 -> 24; Roe 124 -> 104).  The phases' few integer instructions cost
-// less: 256^3 box step HLLC 1126 -> 1103 us, with fluxes 1223 -> 1177; Roe
-// 1540 -> 1509 and 1656 -> 1636; 256 x 128 x 128 cells of ghosted groups with
-// fluxes HLLC 345 -> 326, Roe 459 -> 442; a batched box 328 -> 313.
-HY_DEV int here(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 // WAVES = minimum waves per SIMD the register allocation must allow: 2 gives
 // one workgroup per CU without spills, 4 gives two workgroups per CU (with
 // some spilling); the autotuner picks per specialization.

@@ -65,6 +65,11 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
 
   const int tid = threadIdx.x;
   const Column<int> col = column_of<G>(tid);
+  // the thread number for a phase's task decode
+  auto lane = [&]() -> int {
+    if constexpr (sizeof(T) == 4 && RS != 3 && FLUX) return here(tid);
+    else return tid;
+  };
   const int pcol = (col.y + G) * N + (col.x + G);
   const int qcol = (col.x + G) * N + (col.y + G);
   const int sqx = (col.y + 1) * 18 + (col.x + 1);  // the cross cell in the x arrays
@@ -230,7 +235,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
       __syncthreads();
 
       // ---- B: limited slopes along x and y ---------------------------------
-      for (int q = tid; q < 2 * nS; q += NT) {
+      for (int q = lane(); q < 2 * nS; q += NT) {
         const bool d = q >= nS;
         const int r = d ? q - nS : q;
         const int aa = r % wS + a0S, b = r / wS - 1;
@@ -242,7 +247,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
       __syncthreads();
 
       // ---- C: x and y face states (frame of d) -----------------------------
-      for (int q = tid; q < 2 * kSQ; q += NT) {
+      for (int q = lane(); q < 2 * kSQ; q += NT) {
         const bool d = q >= kSQ;
         const int r = d ? q - kSQ : q;
         const int aa = r % 18 - 1, b = r / 18 - 1;
@@ -320,7 +325,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
         zhp = zfp;
       }
       if (t >= 0 && t < nzt) {
-        for (int q = NT - 1 - tid; q < 2 * kF2; q += NT) {
+        for (int q = NT - 1 - lane(); q < 2 * kF2; q += NT) {
           const bool d = q >= kF2;
           const int r = d ? q - kF2 : q;
           const int i = r % 17 - 1, b = r / 17;  // face between cells i and i+1 of row b
@@ -336,7 +341,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
 
       // ---- F: update plane t-1; flux differences of plane t; face fluxes ---
       if (interior) {
-        const int x = col.x, y = col.y;
+        const int yx = lane(), x = yx & 15, y = yx >> 4;
         if (t >= 1) {
           V5<T> u = ucons(t - 1);
           // plane t-1 lies in the item's group (t-1)/16, at its z = (t-1)%16
@@ -354,7 +359,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
         }
         if (FO) {
           // z face z0 + t of the group (a chunk's last face is the next one's first)
-          const int p = z0 + t, yx = tid;  // tid = y 16 + x
+          const int p = z0 + t, yx = lane();  // y 16 + x
           if constexpr (ZR <= 1) {
             const int f = (p == 0) ? 0 : (p == 16 ? 1 : (p == 8 && a.nf == 3 ? 2 : -1));
             if (f >= 0 && (t >= 0 && (t < nzt || p == 16))) {
@@ -379,7 +384,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
           }
         }
       } else if (FO && t >= 0 && t < nzt) {
-        const int q = tid - 256;
+        const int q = lane() - 256;
         if (q < 2 * a.nf * 16) {
           const bool d = q >= a.nf * 16;
           const int f = (q / 16) % a.nf, s = q % 16;
