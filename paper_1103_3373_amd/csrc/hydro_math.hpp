@@ -552,13 +552,19 @@ HY_DEV V5<T> hlle(const V5<T>& L, const V5<T>& R, const Phys<T>& ph) {
 template <typename T>
 HY_DEV V5<T> hllc(const V5<T>& L, const V5<T>& R, const Phys<T>& ph) {
   if constexpr (!FastMath<T>::on) {
-    // With S* the contact speed and K the side it selects, the flux is
-    // S* U* + p* (0, 1, 0, 0, S*) with m = rho (S - u) and
-    //   rho* = m / (S - S*),  p* = p + m (S* - u),
-    //   (S - S*) E* = (S - u) E - p u + p* S*
-    // (the jump conditions across the wave S); the physical flux of a
-    // supersonic side is the same at S* = u.  5 quotients instead of 9: 96^3
-    // cells of FP64 CTU 237 -> 219 us per step.
+    // With S* the contact speed and K the side it selects, a supersonic side
+    // gives its physical flux, exactly as rounded there; otherwise the jump
+    // conditions across the wave S give, with x = (S* - u) / (S - S*),
+    //   rho* - rho = rho x,  p* = p + rho (S - u) (S* - u),
+    //   E* - E = x E + (p* S* - p u) / (S - S*)
+    // and the flux F + S (U* - U) = S* U* + p* (0, 1, 0, 0, S*).  5 quotients
+    // instead of 9: 96^3 cells of FP64 CTU 237 -> 220 us per step.  Against
+    // 113-bit arithmetic (2 million pairs of states in each of seven classes:
+    // Mach 0.001 to 30, jumps of 0.1% to a factor of 4) the mean error is no
+    // larger than that of the definition's U* in any component, and a quarter
+    // of it in mass and energy below Mach 0.6.  (With m / (S - S*) S* on
+    // supersonic sides as well, 216 us, the error there was 1.2 to 1.7 times
+    // the physical flux's, and the flux NaN where S rounds to u.)
     T SL, SR;
     einfeldt(L, R, ph, SL, SR);
     const T dL = SL - L[1], dR = SR - R[1], mL = L[0] * dL, mR = R[0] * dR;
@@ -566,15 +572,16 @@ HY_DEV V5<T> hllc(const V5<T>& L, const V5<T>& R, const Phys<T>& ph) {
     const bool supL = SL >= T(0), supR = SR <= T(0);
     const bool left = supL || (!supR && Sm >= T(0));
     const V5<T> W = left ? L : R;
-    const T d = left ? dL : dR, m = left ? mL : mR;
-    const T Ss = supL || supR ? W[1] : Sm;
-    const T E = total_energy(W, ph), du = Ss - W[1], r = vrcp(d - du), ps = W[4] + m * du;
-    V5<T> F;
-    F[0] = m * r * Ss;
-    F[1] = F[0] * Ss + ps;
+    const T E = total_energy(W, ph);
+    V5<T> F = flux_with_energy(W, E);
+    if (supL || supR) return F;
+    const T S = left ? SL : SR, m = left ? mL : mR;
+    const T du = Sm - W[1], r = vrcp(S - Sm), x = du * r, ps = W[4] + m * du;
+    F[0] = F[0] + S * (W[0] * x);
+    F[1] = F[0] * Sm + ps;
     F[2] = F[0] * W[2];
     F[3] = F[0] * W[3];
-    F[4] = Ss * (r * (E * d - W[4] * W[1] + ps * Ss) + ps);
+    F[4] = Sm * (E + (x * E + (ps * Sm - W[4] * W[1]) * r) + ps);
     return F;
   }
   T EL = total_energy(L, ph), ER = total_energy(R, ph);
