@@ -1,8 +1,8 @@
 // Launch helpers of the fused kernels with the exact Riemann solver, shared by
 // the two files that instantiate them.  Ghosted groups only.  The paper-style
 // kernel, one workgroup of 256 threads per group with its face states in global
-// memory, took 1,128 us for 16 groups (MHM, PLM, FP64) against 69 here (16
-// workgroups per group).
+// memory, took 1,136 us a call for 16 groups (MHM, PLM, FP64, ghost fill included)
+// against 86 here (16 workgroups per group).
 #pragma once
 
 #include "fused_muscl.hpp"

@@ -25,10 +25,12 @@ template <typename T> HY_DEV T xpow(T a, T b);
 template <> HY_DEV double xpow<double>(double a, double b) { return pow(a, b); }
 template <> HY_DEV float xpow<float>(float a, float b) { return powf(a, b); }
 
-// f_K(p) and its derivative.  On the rarefaction branch the derivative's power
-// p/p_K^-(gamma+1)/(2 gamma) is the one of f_K over p/p_K: one power a side.
+// f_K(p) and its derivative.  The derivative on the rarefaction branch takes a
+// power of its own: from the other, as t / (pr rho_K c_K), it would be 0 / 0
+// where the pressure underflows next to vacuum, and its other rounding changes
+// which solves stop within the tolerance.  (g1 and g2: the two powers.)
 template <typename T>
-HY_DEV void exact_pfun(T p, T rk, T pk, T ck, T gm1, T gp1, T g1, T& f, T& df) {
+HY_DEV void exact_pfun(T p, T rk, T pk, T ck, T gm1, T gp1, T g1, T g2, T& f, T& df) {
   if (p > pk) {  // shock
     const T A = T(2) / (gp1 * rk);
     const T B = gm1 / gp1 * pk;
@@ -37,9 +39,8 @@ HY_DEV void exact_pfun(T p, T rk, T pk, T ck, T gm1, T gp1, T g1, T& f, T& df) {
     df = q * (T(1) - T(0.5) * (p - pk) / (B + p));
   } else {  // rarefaction
     const T pr = p / pk;
-    const T t = xpow<T>(pr, g1);
-    f = T(2) * ck / gm1 * (t - T(1));
-    df = t / (pr * rk * ck);
+    f = T(2) * ck / gm1 * (xpow<T>(pr, g1) - T(1));
+    df = T(1) / (rk * ck) * xpow<T>(pr, g2);
   }
 }
 
@@ -56,7 +57,7 @@ __device__ __attribute__((noinline)) ExactFlux<T> exact_solve(V5<T> L, V5<T> R, 
   ph.gamma = gamma;
   ph.gm1 = gm1;
   ph.inv_gm1 = inv_gm1;
-  const T gp1 = gamma + T(1), g1 = gm1 / (T(2) * gamma);
+  const T gp1 = gamma + T(1), g1 = gm1 / (T(2) * gamma), g2 = -gp1 / (T(2) * gamma);
   const T cL = sqrt(gamma * L[4] / L[0]), cR = sqrt(gamma * R[4] / R[0]);
   const T du = R[1] - L[1];
   ExactFlux<T> r;
@@ -74,8 +75,8 @@ __device__ __attribute__((noinline)) ExactFlux<T> exact_solve(V5<T> L, V5<T> R, 
     T fL, dL, fR, dR;
     int it = 0;
     for (; it < 200; ++it) {
-      exact_pfun(p, L[0], L[4], cL, gm1, gp1, g1, fL, dL);
-      exact_pfun(p, R[0], R[4], cR, gm1, gp1, g1, fR, dR);
+      exact_pfun(p, L[0], L[4], cL, gm1, gp1, g1, g2, fL, dL);
+      exact_pfun(p, R[0], R[4], cR, gm1, gp1, g1, g2, fR, dR);
       T pn = p - (fL + fR + du) / (dL + dR);
       if (pn < T(0)) pn = T(1e-12) * p;
       const T ch = T(2) * fabs(pn - p) / (pn + p);
@@ -83,8 +84,8 @@ __device__ __attribute__((noinline)) ExactFlux<T> exact_solve(V5<T> L, V5<T> R, 
       if (ch < tol) break;
     }
     if (it >= 200) r.fail = 1;
-    exact_pfun(p, L[0], L[4], cL, gm1, gp1, g1, fL, dL);
-    exact_pfun(p, R[0], R[4], cR, gm1, gp1, g1, fR, dR);
+    exact_pfun(p, L[0], L[4], cL, gm1, gp1, g1, g2, fL, dL);
+    exact_pfun(p, R[0], R[4], cR, gm1, gp1, g1, g2, fR, dR);
     u = T(0.5) * (L[1] + R[1]) + T(0.5) * (fR - fL);
   }
   // Sample the solution on the face, x/t = 0: on the side K of the contact,
