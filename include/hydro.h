@@ -115,6 +115,10 @@ int hydro_solve_groups(const void* in, void* out, void* flux_out, int n_groups, 
  *   dt = cfl * dh / max over cells of max_d(|v_d| + c).
  * Written to dt_out (device, 1 double).  The maximum is order-free, so the
  * result equals a serial FP64 evaluation on the same (upcast) data.
+ * This call, hydro_conserved_sums and hydro_cfl_dt_sums share scratch memory
+ * per stream: graphs captured on one stream that hold such calls must not run
+ * at the same time as each other or as that stream's own calls (their results
+ * would be undefined; calls after that are not affected).
  */
 int hydro_cfl_dt(const void* U, int n_groups, double dh, double gamma, double cfl, int flags, double* dt_out,
                  void* stream);

@@ -58,17 +58,13 @@ struct Workspace {
   long long seg_partial_n = 0;
   void* vl = nullptr;  // VL half-step scratch (fused path)
   size_t vl_bytes = 0;
-  double* partial = nullptr;  // reduction partials, kPartials x 6 doubles, then counters (a pool slot or own memory)
+  double* partial = nullptr;  // reduction partials and counters (a pool slot or own memory)
   bool own_partial = false;
-  unsigned next_done = 0;     // counter of the next reduction
 };
 const int kPartialSlots = 64;
-const int kPartials = 1024;  // reduction partials (at most; the number depends on the group count alone)
-// A reduction counts its finished workgroups in one of kDone zeroed sets of
-// counters, taken in turn: reductions captured into graphs keep theirs, so
-// graphs that were captured on one stream and replayed on several share none.
-const int kDone = 32;
-const size_t kPartialBytes = (size_t)kPartials * 6 * sizeof(double) + kDone * hy::kDoneSet * sizeof(unsigned);
+// 6 partials of each workgroup of a reduction, then its arrival counters.
+const size_t kPartialDoubles = (size_t)hy::kReduceMax * 6;
+const size_t kPartialBytes = kPartialDoubles * sizeof(double) + hy::kDoneSet * sizeof(unsigned);
 struct DeviceState {
   unsigned long long* diag = nullptr;
   double* partial_pool = nullptr;
@@ -158,11 +154,10 @@ int reduce_state(const void* U, int n_groups, double dh, double gamma, double cf
   if (int rc = device_state(&ds)) return rc;
   Workspace& w = ds->ws[st];
   if (int rc = ensure_partial(*ds, w)) return rc;
-  unsigned* done = reinterpret_cast<unsigned*>(w.partial + (size_t)kPartials * 6) + w.next_done++ % kDone * hy::kDoneSet;
-  hipError_t e = (flags & HYDRO_F64) ? hy::launch_reduce((const double*)U, n_groups, dh, gamma, cfl, w.partial,
-                                                         kPartials, done, dt_out, sums_out, st)
-                                     : hy::launch_reduce((const float*)U, n_groups, dh, gamma, cfl, w.partial,
-                                                         kPartials, done, dt_out, sums_out, st);
+  unsigned* done = reinterpret_cast<unsigned*>(w.partial + kPartialDoubles);
+  hipError_t e = (flags & HYDRO_F64)
+                     ? hy::launch_reduce((const double*)U, n_groups, dh, gamma, cfl, w.partial, done, dt_out, sums_out, st)
+                     : hy::launch_reduce((const float*)U, n_groups, dh, gamma, cfl, w.partial, done, dt_out, sums_out, st);
   if (e != hipSuccess) return hip_fail(e, what);
   return 0;
 }

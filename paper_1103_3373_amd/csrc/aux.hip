@@ -7,6 +7,7 @@
 //    conserved sums with a fixed reduction order, in one launch; the time steps
 //    of a segment table in two.
 
+#include <algorithm>
 #include <type_traits>
 
 #include "hydro_internal.h"
@@ -963,7 +964,7 @@ hipError_t launch_seg_dt(const Seg* segs, int n_segs, long long n_groups, double
 // The partials pass between workgroups on different XCDs, whose L2 caches are
 // not coherent for plain accesses: they are stored and loaded as device-scope
 // atomics, and a workgroup counts itself as done only after its stores have
-// been acknowledged.  The counters wrap to zero by themselves.
+// been acknowledged.
 // ---------------------------------------------------------------------------
 enum { kRedDt = 1, kRedSums = 2 };
 
@@ -1026,11 +1027,9 @@ __global__ void __launch_bounds__(256) reduce_kernel(const T* __restrict__ U, lo
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's stores have reached the device's memory
     if (tid == 0) {
-      // Workgroup b counts in counter b mod 16, the last of each in the main
-      // one: increments of one address take about 10 ns each, one after another.
-      const unsigned k = blockIdx.x % kDoneLeaves, n = (unsigned)P / kDoneLeaves + (k < (unsigned)P % kDoneLeaves);
-      const unsigned leaves = (unsigned)P < kDoneLeaves ? (unsigned)P : kDoneLeaves;
-      last = atomicInc(done + (k + 1) * kDoneStride, n - 1u) == n - 1u && atomicInc(done, leaves - 1u) == leaves - 1u;
+      const unsigned w = arrival_weight(blockIdx.x, P);
+      last = arrival_completes(atomicAdd(done + arrival_leaf(blockIdx.x), w), w, kLeafSum) &&
+             arrival_completes(atomicAdd(done, 1u), 1u, kDoneLeaves);
     }
   }
   __syncthreads();
@@ -1059,12 +1058,11 @@ __global__ void __launch_bounds__(256) reduce_kernel(const T* __restrict__ U, lo
 
 template <typename T, int MODE>
 static hipError_t launch_reduce_mode(const T* U, long long n_groups, double dh, double gamma, double cfl,
-                                     double* partial, int max_partial, unsigned* done, double* dt_out,
-                                     double* sums_out, hipStream_t st) {
-  const long long n_chunks = 4 * n_groups;
-  if (n_groups < 2048) max_partial /= 2;
+                                     double* partial, unsigned* done, double* dt_out, double* sums_out,
+                                     hipStream_t st) {
+  const long long n_chunks = 4 * n_groups, max_partial = n_groups < 2048 ? kReduceMax / 2 : kReduceMax;
   const long long per = (n_chunks + max_partial - 1) / max_partial > 0 ? (n_chunks + max_partial - 1) / max_partial : 1;
-  const long long P = (n_chunks + per - 1) / per > 0 ? (n_chunks + per - 1) / per : 1;  // no groups: one workgroup
+  const long long P = std::max((n_chunks + per - 1) / per, (long long)kDoneLeaves);
   auto k = (uintptr_t)U % 16 == 0 ? reduce_kernel<T, MODE, true> : reduce_kernel<T, MODE, false>;
   k<<<dim3((unsigned)P), dim3(256), 0, st>>>(U, n_chunks, per, gamma, cfl * dh, dh * dh * dh, partial, done, dt_out,
                                             sums_out);
@@ -1073,17 +1071,16 @@ static hipError_t launch_reduce_mode(const T* U, long long n_groups, double dh, 
 
 template <typename T>
 hipError_t launch_reduce(const T* U, long long n_groups, double dh, double gamma, double cfl, double* partial,
-                         int max_partial, unsigned* done, double* dt_out, double* sums_out, hipStream_t st) {
+                         unsigned* done, double* dt_out, double* sums_out, hipStream_t st) {
   if (dt_out && sums_out)
-    return launch_reduce_mode<T, kRedDt | kRedSums>(U, n_groups, dh, gamma, cfl, partial, max_partial, done, dt_out,
-                                                    sums_out, st);
+    return launch_reduce_mode<T, kRedDt | kRedSums>(U, n_groups, dh, gamma, cfl, partial, done, dt_out, sums_out, st);
   if (dt_out)
-    return launch_reduce_mode<T, kRedDt>(U, n_groups, dh, gamma, cfl, partial, max_partial, done, dt_out, sums_out, st);
-  return launch_reduce_mode<T, kRedSums>(U, n_groups, dh, gamma, cfl, partial, max_partial, done, dt_out, sums_out, st);
+    return launch_reduce_mode<T, kRedDt>(U, n_groups, dh, gamma, cfl, partial, done, dt_out, sums_out, st);
+  return launch_reduce_mode<T, kRedSums>(U, n_groups, dh, gamma, cfl, partial, done, dt_out, sums_out, st);
 }
-template hipError_t launch_reduce<float>(const float*, long long, double, double, double, double*, int, unsigned*,
+template hipError_t launch_reduce<float>(const float*, long long, double, double, double, double*, unsigned*,
                                          double*, double*, hipStream_t);
-template hipError_t launch_reduce<double>(const double*, long long, double, double, double, double*, int, unsigned*,
+template hipError_t launch_reduce<double>(const double*, long long, double, double, double, double*, unsigned*,
                                           double*, double*, hipStream_t);
 
 }  // namespace hy

@@ -6,6 +6,7 @@
 
 #include <atomic>
 
+#include "arrivals.hpp"
 #include "hydro_math.hpp"
 
 namespace hy {
@@ -144,13 +145,10 @@ hipError_t launch_fill_interp(const T* coarse, int cn, const int* layout, long l
 hipError_t launch_seg_dt(const Seg* segs, int n_segs, long long n_groups, double gamma, double cfl, int f64,
                          double* partial, hipStream_t st);
 // dt (dt_out, may be null) and conserved sums (sums_out, may be null) of
-// n_groups interiors.  partial: 6 max_partial doubles; done: a zeroed set of
-// counters that no other launch in flight uses (zero again afterwards): a main
-// one and kDoneLeaves, each on a cache line of its own.
-constexpr unsigned kDoneLeaves = 16, kDoneStride = 16;
-constexpr unsigned kDoneSet = (kDoneLeaves + 1) * kDoneStride;
+// n_groups interiors.  partial: 6 kReduceMax doubles; done: a set of counters,
+// zero before its first use, that no other launch in flight uses.
 template <typename T>
 hipError_t launch_reduce(const T* U, long long n_groups, double dh, double gamma, double cfl, double* partial,
-                         int max_partial, unsigned* done, double* dt_out, double* sums_out, hipStream_t st);
+                         unsigned* done, double* dt_out, double* sums_out, hipStream_t st);
 
 }  // namespace hy
