@@ -82,19 +82,33 @@ int current_device(int* dev) {
   return 0;
 }
 
+// Device memory, zero for every stream: the clearing is on the null stream, which
+// non-blocking streams do not wait for.
+hipError_t malloc_zeroed(void** p, size_t bytes) {
+  *p = nullptr;
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess) return e;
+  e = hipMemset(*p, 0, bytes);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  if (e != hipSuccess) {
+    hipFree(*p);
+    *p = nullptr;
+  }
+  return e;
+}
+
 // Returns the device state (creating the diagnostics counters on first use).
 int device_state(DeviceState** out) {
   int dev;
   if (int rc = current_device(&dev)) return rc;
   DeviceState& d = g_dev[dev];
   if (!d.diag) {
-    hipError_t e = hipMalloc((void**)&d.diag, 2 * sizeof(unsigned long long));
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc(diag)");
-    e = hipMemset(d.diag, 0, 2 * sizeof(unsigned long long));
-    if (e != hipSuccess) return hip_fail(e, "hipMemset(diag)");
-    e = hipMalloc((void**)&d.partial_pool, kPartialSlots * kPartialBytes);
-    if (e == hipSuccess) e = hipMemset(d.partial_pool, 0, kPartialSlots * kPartialBytes);  // counters
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc(partial pool)");
+    hipError_t e = malloc_zeroed((void**)&d.diag, 2 * sizeof(unsigned long long));
+    if (e != hipSuccess) return hip_fail(e, "diagnostics counters");
+  }
+  if (!d.partial_pool) {
+    hipError_t e = malloc_zeroed((void**)&d.partial_pool, kPartialSlots * kPartialBytes);
+    if (e != hipSuccess) return hip_fail(e, "partial pool");
   }
   *out = &d;
   return 0;
@@ -135,13 +149,9 @@ int ensure_partial(DeviceState& d, Workspace& w) {
     w.partial = reinterpret_cast<double*>(reinterpret_cast<char*>(d.partial_pool) + d.partial_used++ * kPartialBytes);
     return 0;
   }
-  void* p = nullptr;
-  hipError_t e = hipMalloc(&p, kPartialBytes);
-  if (e == hipSuccess) e = hipMemset(p, 0, kPartialBytes);
-  if (e != hipSuccess) {
-    hipFree(p);
-    return hip_fail(e, "hipMalloc(partials)");
-  }
+  void* p;
+  hipError_t e = malloc_zeroed(&p, kPartialBytes);
+  if (e != hipSuccess) return hip_fail(e, "reduction partials");
   w.partial = static_cast<double*>(p);
   w.own_partial = true;
   return 0;
