@@ -342,7 +342,9 @@ int hydro_solve_batch(const struct hydro_seg* segs, int n_segs, long long n_grou
  * Autotuner: times the fused kernel's launch shapes for `spec` on a
  * synthetic batch of n_groups_hint groups (allocates and frees its own
  * buffers; synchronizes `stream`) and records the fastest in the in-process
- * cache used by hydro_solve_groups / hydro_solve_batch.  If the environment
+ * cache used by hydro_solve_groups / hydro_solve_batch / hydro_step_box.  It
+ * times whole groups, so launches that split their groups for want of them
+ * (see hydro_set_launch_shape) do so whatever is recorded.  If the environment
  * variable HYDRO_TUNE_CACHE names a file, the cache is appended there and
  * read back at the first call.  Returns the chosen workgroup count (> 0).
  */
@@ -350,7 +352,7 @@ int hydro_autotune(const struct hydro_spec* spec, int n_groups_hint, void* strea
 
 /*
  * Pins the launch shape of the fused kernel for `spec`'s specialization in
- * the in-process cache (as if the autotuner had chosen it), for callers that
+ * the in-process cache, in place of what the autotuner chose, for callers that
  * tune offline or need a fixed shape.  grid = persistent workgroup count (0
  * = default: one or twelve workgroups per compute unit, by variant; a grid
  * larger than a launch's work-item count is clamped to it).  variant =

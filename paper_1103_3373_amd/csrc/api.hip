@@ -204,6 +204,7 @@ struct Tune {
   int waves;     // 2 or 4
   int zrun;      // CTU box steps: groups per z-run (0 = default)
   int grid_box;  // CTU box steps: workgroups (0 = as grid)
+  bool pinned = false;  // by hydro_set_launch_shape
   int zsplit = 1;       // workgroups per group along z (chosen per launch, never stored)
   int zsplit_pred = 1;  // the same of the VL predictor
 };
@@ -269,14 +270,14 @@ int split_for(long long n, int slots, double extra, bool shared) {
   return best;
 }
 
-Tune tuned(int f64, int scheme, int recon, int riemann, int charlim, long long n_groups) {
-  tune_load();
-  auto it = g_tune.find(tune_key(f64, scheme, recon, riemann, charlim));
-  // Untuned default: the two-workgroups-per-CU register variant with twelve
-  // workgroups per CU over the persistent loop (about the autotuner's choice
-  // for CTU on MI355X: more, shorter workgroups even out the tail); FP64 has
-  // one variant only.
-  Tune t = (it != g_tune.end()) ? it->second : Tune{0, 4, 0, 0};
+// Untuned default: the two-workgroups-per-CU register variant with twelve
+// workgroups per CU over the persistent loop (about the autotuner's choice
+// for CTU on MI355X: more, shorter workgroups even out the tail); FP64 has
+// one variant only.
+const Tune kUntuned{0, 4, 0, 0};
+
+// A shape's register variant and grid for n_groups work items.
+Tune resolve(Tune t, int f64, long long n_groups) {
   if (f64) t.waves = 2;
   if (t.grid <= 0) t.grid = cu_count() * (t.waves == 4 ? 12 : 1);
   if (t.grid > n_groups) t.grid = (int)n_groups;
@@ -294,13 +295,34 @@ Tune split_small(Tune t, int f64, int scheme, long long n_groups, bool shared = 
   return t;
 }
 
+// The stored shape (tuned or pinned) for a launch of n_groups, if it applies.
+// The autotuner times whole groups at one group count, so its shape is not for
+// launches that the untuned shape splits (FP32 CTU, 8 groups: 120 us whole in
+// either variant, 28 split); a pinned shape applies to all.
+const Tune* stored(int f64, int scheme, int recon, int riemann, int charlim, long long n_groups, bool shared) {
+  tune_load();
+  auto it = g_tune.find(tune_key(f64, scheme, recon, riemann, charlim));
+  if (it == g_tune.end()) return nullptr;
+  if (!it->second.pinned &&
+      split_small(resolve(kUntuned, f64, n_groups), f64, scheme, n_groups, shared).zsplit > 1)
+    return nullptr;
+  return &it->second;
+}
+
+// Launch shape of a launch over n_groups groups.
+Tune tuned(int f64, int scheme, int recon, int riemann, int charlim, long long n_groups, bool shared = false) {
+  const Tune* t = stored(f64, scheme, recon, riemann, charlim, n_groups, shared);
+  return split_small(resolve(t ? *t : kUntuned, f64, n_groups), f64, scheme, n_groups, shared);
+}
+
 // Launch shape of a step over one periodic box of ngz groups in z
-// (n_groups in all): the z-run length (the tuned one,
+// (n_groups in all): the z-run length (the stored one,
 // or the largest of 4, 2 that divides ngz and still leaves two runs per
 // resident workgroup slot; in any case the largest built length, not above
 // it, that divides ngz) and the grid over the runs.
 Tune tuned_box(int f64, int scheme, int recon, int riemann, int limiter, int charlim, long long n_groups, int ngz) {
-  Tune t = tuned(f64, scheme, recon, riemann, charlim, n_groups);
+  const Tune* s = stored(f64, scheme, recon, riemann, charlim, n_groups, false);
+  Tune t = resolve(s ? *s : kUntuned, f64, n_groups);
   int K = t.zrun;
   if (K <= 0) {
     const long long slots = (long long)cu_count() * (t.waves == 4 ? 2 : 1);
@@ -445,8 +467,7 @@ int hydro_solve_groups(const void* in, void* out, void* flux_out, int n_groups, 
   }
   // Fused path: a single segment passed by value, host dt included.
   hy::Seg seg{in, out, flux_out, nullptr, 1.0, dh, 0, n_groups, 0, 0, 0, 0};
-  const Tune tu = split_small(tuned(f64, scheme, reconstruction, riemann, (flags & HYDRO_CHAR) ? 1 : 0, n_groups), f64,
-                              scheme, n_groups);
+  const Tune tu = tuned(f64, scheme, reconstruction, riemann, (flags & HYDRO_CHAR) ? 1 : 0, n_groups);
   if (int rc = ensure_vl(w, (size_t)n_groups * hy::fused_scratch_per_group(scheme, reconstruction, 0) * esz)) return rc;
   if (f64)
     return run_fused<double>(nullptr, 1, n_groups, g, scheme, reconstruction, riemann, limiter, flags, gamma,
@@ -476,8 +497,7 @@ int hydro_solve_batch(const struct hydro_seg* segs, int n_segs, long long n_grou
   if (int rc = device_state(&ds)) return rc;
   const bool f64 = (spec->flags & HYDRO_F64) != 0;
   const int g = ghost_width(spec->scheme, spec->reconstruction);
-  const Tune tu = split_small(tuned(f64, spec->scheme, spec->reconstruction, spec->riemann, charlim, n_groups_total),
-                              f64, spec->scheme, n_groups_total, true);
+  const Tune tu = tuned(f64, spec->scheme, spec->reconstruction, spec->riemann, charlim, n_groups_total, true);
   Workspace& w = ds->ws[st];
   const int box_segs = (spec->flags & HYDRO_BOX_SEGS) ? 1 : 0;
   if (int rc = ensure_vl(w, (size_t)n_groups_total *
@@ -795,7 +815,8 @@ int hydro_set_launch_shape(const struct hydro_spec* spec, int grid, int variant,
   const int charlim = (spec->flags & HYDRO_CHAR) ? 1 : 0;
   std::lock_guard<std::mutex> lock(g_mu);
   tune_load();
-  g_tune[tune_key(f64, spec->scheme, spec->reconstruction, spec->riemann, charlim)] = Tune{grid, variant, zrun, grid};
+  g_tune[tune_key(f64, spec->scheme, spec->reconstruction, spec->riemann, charlim)] =
+      Tune{grid, variant, zrun, grid, true};
   return 0;
 }
 
