@@ -368,7 +368,7 @@ int hydro_autotune(const struct hydro_spec* spec, int n_groups_hint, void* strea
  * PPM); the depth used is the largest built one, not above the request, that
  * divides the box's group count in z.  A launch of one group per workgroup
  * with too few groups to fill the device splits each group's planes over
- * several workgroups (variant 4 in FP32, 2 in FP64, no smaller grid pinned);
+ * several workgroups (variant 4 in FP32, 2 in FP64, no grid pinned);
  * hydro_get_launch_shape reports the workgroups it uses.  At one tile depth,
  * results and diagnostic counts do not depend on the grid, the variant or a
  * split (bit for bit).  Tile depths differ in the

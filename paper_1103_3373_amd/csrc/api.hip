@@ -286,9 +286,9 @@ Tune resolve(Tune t, int f64, long long n_groups) {
 }
 
 // Splits the groups of a one-group-per-item launch along z where it has too
-// few of them (and no smaller grid is pinned).
+// few of them, unless a grid is pinned (grid_box is that grid) or a smaller one tuned.
 Tune split_small(Tune t, int f64, int scheme, long long n_groups, bool shared = false) {
-  if (t.grid < n_groups || t.waves != hy::split_waves(f64)) return t;
+  if (t.grid < n_groups || (t.pinned && t.grid_box > 0) || t.waves != hy::split_waves(f64)) return t;
   t.zsplit = split_for(n_groups, f64 ? 1 : 2, 3.4, shared);
   t.grid = (int)(n_groups * t.zsplit);
   if (scheme == HYDRO_VL) t.zsplit_pred = split_for(n_groups, 2, 1.5, shared);

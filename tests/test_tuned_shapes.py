@@ -51,3 +51,22 @@ s = Spec(2, 1, 1, 1, CHAR, 1.4)
 assert shape(s, 32, 32, 32) == (128, 4, 1)
 assert shape(s, 256, 256, 256) == (512, 2, 1)
 """)
+
+
+def test_pinned_grid_is_used(tmp_path):
+    """A pinned grid is the number of workgroups, clamped to the groups; only
+    without one are groups split."""
+    run(tmp_path, COMMON + """
+for scheme in (0, 1, 2):
+    for flags, waves in ((CHAR, 4), (CHAR | F64, 2)):
+        s = Spec(scheme, 1, 1, 1, flags, 1.4)
+        for grid in (5, 8, 9, 128, 4096):
+            assert L.hydro_set_launch_shape(ctypes.byref(s), grid, waves, 0) == 0
+            want = min(grid, 8)
+            assert shape(s, 32, 32, 32) == (want, waves, 1), (scheme, flags, grid)
+            calls()
+            groups(s, 8), box(s, 32)
+            assert {g for k, g in launched()} == {want}, (scheme, flags, grid)
+        assert L.hydro_set_launch_shape(ctypes.byref(s), 0, waves, 0) == 0
+        assert shape(s, 32, 32, 32) == (128, waves, 1)
+""")
