@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "fill_order.hpp"
 #include "hydro_internal.h"
 
 namespace hy {
@@ -30,17 +31,16 @@ template <typename T> __device__ __forceinline__ void store16(T* dst, int q, con
 // division per cell); GC == 0: g taken at run time.
 //
 // Bound by memory: 20 B written per ghosted FP32 cell and 20 B read, the reads
-// of ghost layers from L2.  Workgroups are dispatched to the 8 XCDs
-// round-robin, so XCD x takes the x-th eighth of the groups, whose neighbours
-// then share its L2 (the planes of one group used to spread over all of them).
+// of ghost layers from L2, which fill_order.hpp's order by XCD keeps local.
 // WIDE (out 16-byte aligned; an N x N plane is a multiple of that): the planes
 // are passed through LDS and stored 16 bytes a lane, around the caches, which
-// the output would sweep of the input.  g = 3, FP32, plain box: 128^3 cells 49
-// -> 25 us, 192^3 198 -> 79 (148 through the caches), 256^3 480 -> 328 (396).
-// Below 64 groups (4 us) neither pays.
+// the output would sweep of the input.  Both together, g = 3, FP32, plain box:
+// 128^3 cells 49 -> 25 us, 192^3 198 -> 79 (148 through the caches), 256^3 480
+// -> 322 (396).  Below 64 groups (4 us) neither pays.
 template <typename T, int GC, bool WIDE>
 __global__ void __launch_bounds__(512) fill_periodic_kernel(const T* __restrict__ box, int nx, int ny, int nz, int g_rt,
-                                                            int grouped, T* __restrict__ out, long long g_off, int cnt) {
+                                                            int grouped, T* __restrict__ out, long long g_off, int cnt,
+                                                            bool by_xcd) {
   // A workgroup fills planes k and k + 1 of a padded group (N = 16 + 2g is
   // even; k even), all ten loads of a thread issued before its stores; threads
   // cover the N x N plane, x fastest.  Group counts stay below 2^31 (the caller
@@ -49,11 +49,9 @@ __global__ void __launch_bounds__(512) fill_periodic_kernel(const T* __restrict_
   const int g = GC > 0 ? GC : g_rt;
   const int N = 16 + 2 * g;
   const long long nc = (long long)N * N * N;
-  const unsigned H = N / 2, chunk = (cnt + 7) / 8;  // groups of an XCD
-  const bool by_xcd = gridDim.x != (unsigned)cnt * H;
-  const unsigned w = by_xcd ? blockIdx.x / 8 : blockIdx.x;
-  const unsigned gl = w / H + (by_xcd ? blockIdx.x % 8 * chunk : 0u);
-  const int k = 2 * (int)(w % H);
+  const FillItem it = fill_item(blockIdx.x, cnt, N / 2, by_xcd);
+  const unsigned gl = it.group;
+  const int k = 2 * (int)it.pair;
   if (gl >= (unsigned)cnt) return;  // uniform
   const unsigned G = (unsigned)(g_off + gl);
   const unsigned ngx = (unsigned)nx >> 4, ngy = (unsigned)ny >> 4;
@@ -108,15 +106,15 @@ __global__ void __launch_bounds__(512) fill_periodic_kernel(const T* __restrict_
 template <typename T, int GC>
 static void go_fill_periodic(const T* box, int nx, int ny, int nz, int g, int grouped, T* out, long long g0, int cnt,
                              hipStream_t st) {
-  const bool many = cnt >= 64;
-  const dim3 grid((unsigned)(many ? (cnt + 7) / 8 * 8 : cnt) * (unsigned)(8 + g));
+  const bool many = cnt >= 64, by_xcd = fill_by_xcd(cnt, sizeof(T), g, nx / 16, grouped != 0);
+  const dim3 grid(fill_grid(cnt, 8 + g, by_xcd));
   if constexpr (GC > 0) {
     if (many && (uintptr_t)out % 16 == 0) {
-      fill_periodic_kernel<T, GC, true><<<grid, dim3(512), 0, st>>>(box, nx, ny, nz, g, grouped, out, g0, cnt);
+      fill_periodic_kernel<T, GC, true><<<grid, dim3(512), 0, st>>>(box, nx, ny, nz, g, grouped, out, g0, cnt, by_xcd);
       return;
     }
   }
-  fill_periodic_kernel<T, GC, false><<<grid, dim3(512), 0, st>>>(box, nx, ny, nz, g, grouped, out, g0, cnt);
+  fill_periodic_kernel<T, GC, false><<<grid, dim3(512), 0, st>>>(box, nx, ny, nz, g, grouped, out, g0, cnt, by_xcd);
 }
 
 template <typename T>
