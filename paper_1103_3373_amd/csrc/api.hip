@@ -254,7 +254,12 @@ int cu_count() {
 // at 216 (CTU, FP32).  A larger s has to be 3% better.  A batched launch
 // (shared) may run beside others on other streams, to which the planes a split
 // repeats are lost: it stops at one workgroup per unit (a server tick over 6
-// classes of 64 to 520 groups: 500 us, 549 us with the full rule).
+// classes of 64 to 520 groups on three streams: 500 us, 549 us with the full
+// rule).  The library cannot see whether it does: a batch that runs alone gives
+// up the splits beyond that as well, all of them from half as many groups as
+// units (129 to 256 groups: up to a third by the model).  The VL predictor goes
+// by the same model, two to a unit and 16 planes, which is rough for it: on
+// ghosted groups it marches up to 22 planes, and in FP64 with PPM one fits a unit.
 int split_for(long long n, int slots, double extra, bool shared) {
   const int cus = cu_count();
   int best = 1;

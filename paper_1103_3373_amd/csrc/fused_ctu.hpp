@@ -139,7 +139,12 @@ __global__ void __launch_bounds__(kThreads, WAVES) ctu_fused_kernel(FusedArgs<T>
 
   const int tid = threadIdx.x;
   const Column<int> col = column_of<G>(tid);
-  // the thread number for a phase's task decode
+  // The thread number for a phase's task decode, new to the compiler (here) in the
+  // FP32 kernels, which spill at two workgroups per CU.  FP64 has registers for
+  // the decoded tasks.  The exact solver's kernels are left out: built with it, the
+  // FP64 one gave wrong values (the compiler had put copies of live vector registers
+  // before a join restores exec); tests/test_gpu_exact.py compares these kernels,
+  // whole and split groups with fluxes, with the paper-style one.
   auto lane = [&]() -> int {
     if constexpr (sizeof(T) == 4 && RS != 3) return here(tid);
     else return tid;

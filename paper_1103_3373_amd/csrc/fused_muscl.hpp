@@ -65,7 +65,7 @@ __global__ void __launch_bounds__(kThreads, WAVES) muscl_kernel(FusedArgs<T> a) 
 
   const int tid = threadIdx.x;
   const Column<int> col = column_of<G>(tid);
-  // the thread number for a phase's task decode
+  // the thread number for a phase's task decode (as in the CTU kernel)
   auto lane = [&]() -> int {
     if constexpr (sizeof(T) == 4 && RS != 3 && FLUX) return here(tid);
     else return tid;
