@@ -14,7 +14,7 @@ namespace hy {
 // the launch's own (atomicInc) would leave it between two multiples, and the
 // launches after it would finish early or not at all.
 constexpr unsigned kReduceMax = 1024;                      // workgroups of a launch, at least kDoneLeaves
-constexpr unsigned kDoneLeaves = 16, kDoneStride = 16;     // a cache line of its own for each counter
+constexpr unsigned kDoneLeaves = 16, kDoneStride = 16;     // 64 bytes for each counter (128: no faster)
 constexpr unsigned kDoneSet = (kDoneLeaves + 1) * kDoneStride;  // the main counter, then the leaves
 constexpr unsigned kLeafSum = kReduceMax / kDoneLeaves;
 static_assert((kLeafSum & (kLeafSum - 1)) == 0 && (kDoneLeaves & (kDoneLeaves - 1)) == 0, "the counters wrap at 2^32");
