@@ -953,7 +953,7 @@ hipError_t launch_seg_dt(const Seg* segs, int n_segs, long long n_groups, double
 // the sums are the same whether they are asked for together or apart.
 //
 // Small states are bound by launches (12.2 us with a second launch for the
-// finish and scalar loads, 6.6 us now, at 8 groups), large ones by reading the
+// finish and scalar loads, 6.7 us now, at 8 groups), large ones by reading the
 // state once (4,096 FP32 groups: 81 -> 63 us, 5.4 TB/s; 512: 18.4 -> 13.4).
 // In between, the workgroups' arrivals count: up to 512 of them are as fast as
 // 1,024 below 2,048 groups (512 groups 13.4 against 14.2 us) and slower from

@@ -2,7 +2,7 @@
 // the two files that instantiate them.  Ghosted groups only.  The paper-style
 // kernel, one workgroup of 256 threads per group with its face states in global
 // memory, took 1,136 us a call for 16 groups (MHM, PLM, FP64, ghost fill included)
-// against 86 here (16 workgroups per group).
+// against 85 here (16 workgroups per group).
 #pragma once
 
 #include "fused_muscl.hpp"
